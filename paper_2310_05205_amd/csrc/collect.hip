@@ -22,10 +22,18 @@
 // window's first element in the first requested column writes the draw's
 // slot, start and weight.  A step then needs no separate selection launch.
 //
-// Element width per column: 16 bytes when every window source and output
-// address is 16-byte aligned, else 4 bytes when 4-byte aligned, else 1.
-// Sources are aligned when the column base and the step size are, or, for
-// full-trajectory windows (L = T, every start 0), the trajectory size.
+// Element width per column.  Only the output decides it: window sources may
+// start at any byte, since global loads on gfx950 take any address, and an
+// unaligned wave load touches one cache line more than an aligned one.
+//   16 bytes  when the batch is 16-byte aligned and a window is whole elements,
+//             or holds at least kThreads * unroll * 16 / (kThreads - 2) bytes:
+//             then some elements straddle two windows (copy_straddle);
+//   4 bytes   when the batch and the window are multiples of 4;
+//   1 byte    otherwise (small windows of odd size, unaligned batches).
+// When sources had to be aligned too, steps of 147, 1, 2 and 1 bytes were
+// gathered byte by byte: 3001 windows of 13 steps (5.9 MB) took 29.7 us, now
+// 7.8.  512 windows of 20 steps of 68, 24, 4 and 4 bytes (4-byte elements
+// before, 16-byte ones now) stayed at 5.7 us: they are bound by latency.
 #include "gear_internal.h"
 
 namespace gear {
@@ -69,6 +77,13 @@ constexpr int kMaxLaunchCols = 16;  // columns per launch (more take several lau
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
+// How a column's batch is cut into pieces.
+enum : int32_t {
+    kNarrow = 0,    // several whole windows per piece
+    kWide = 1,      // equal pieces of the batch, each within one or two windows of whole elements
+    kStraddle = 2,  // equal pieces of the batch, an element may cover the end of one window and the start of the next
+};
+
 struct ColTask {
     const uint8_t* src;   // device-visible column base
     uint8_t* out;         // batch output [B][W]
@@ -78,11 +93,11 @@ struct ColTask {
     int64_t piece;        // bytes per piece: kThreads * unroll * width
     int64_t n;            // elements per window, W / width
     int32_t width;        // element bytes: 16, 4 or 1
-    int32_t wide;         // 1: equal pieces of the batch, each within one or two windows;
-                          // 0: several whole windows per piece
+    int32_t layout;       // kNarrow, kWide or kStraddle
     int32_t wpp;          // windows per piece (narrow)
     uint32_t epw;         // elements per window (narrow)
-    uint32_t magic;       // ceil(2^32 / epw) for epw > 1: exact quotient for operands < 2^16
+    uint32_t magic;       // narrow: ceil(2^32 / epw) for epw > 1; straddle: ceil(2^32 / W), or 0 when a
+                          // window holds at least a piece: exact quotient for operands < 2^16
     int32_t draws_out;    // 1: this column's pieces write the selected slots, starts and weights
 };
 
@@ -108,19 +123,23 @@ struct CollectArgs {
     uint32_t* status;
 };
 
+// Element types: `type` in the batch (aligned), `src` in a column (any address).
 template <int WIDTH>
 struct Elem;
 template <>
 struct Elem<16> {
     typedef u32x4 type;
+    typedef u32x4 src __attribute__((aligned(1)));
 };
 template <>
 struct Elem<4> {
     typedef uint32_t type;
+    typedef uint32_t src __attribute__((aligned(1)));
 };
 template <>
 struct Elem<1> {
     typedef uint8_t type;
+    typedef uint8_t src;
 };
 
 // Table bytes are read once per collection and the batch is written once:
@@ -131,8 +150,8 @@ struct Elem<1> {
 // copy of the same bytes.  Plain stores win (81 us) only when the same
 // output buffer is rewritten while the last-level cache still holds it.
 template <int WIDTH>
-__device__ inline typename Elem<WIDTH>::type load_stream(const typename Elem<WIDTH>::type* p) {
-    return __builtin_nontemporal_load(p);
+__device__ inline typename Elem<WIDTH>::type load_stream(const uint8_t* p) {
+    return __builtin_nontemporal_load(reinterpret_cast<const typename Elem<WIDTH>::src*>(p));
 }
 
 template <int WIDTH>
@@ -205,18 +224,17 @@ __device__ void copy_wide(const CollectArgs& a, const DrawArgs& g, const ColTask
         if (r0 == 0) write_draw(g, w0);
         else if (two) write_draw(g, w0 + 1);
     }
-    const V* src = reinterpret_cast<const V*>(c.src);
     V* dst = reinterpret_cast<V*>(c.out) + o0;
-    // Element offsets of the two windows' sources, shifted so that element
-    // r of the piece (r = r0 + e) reads base + r in either window.
-    const int64_t b0 = so0 / WIDTH, b1 = so1 / WIDTH - c.n;
+    // Byte offsets of the two windows' sources, shifted so that element r of
+    // the piece (r = r0 + e) reads base + r * WIDTH in either window.
+    const int64_t b0 = so0, b1 = so1 - c.W;
     V v[U];
     if (m == P && so0 >= 0 && (!two || so1 >= 0)) {
         // Every element valid: the loads go out unconditionally, all in flight.
 #pragma unroll
         for (int k = 0; k < U; k++) {
             const int64_t r = r0 + lane_elem<U>(k);
-            v[k] = load_stream<WIDTH>(src + (r < c.n ? b0 : b1) + r);
+            v[k] = load_stream<WIDTH>(c.src + (r < c.n ? b0 : b1) + r * WIDTH);
         }
 #pragma unroll
         for (int k = 0; k < U; k++) store_stream<WIDTH>(dst + lane_elem<U>(k), v[k]);
@@ -230,7 +248,7 @@ __device__ void copy_wide(const CollectArgs& a, const DrawArgs& g, const ColTask
         const int64_t r = r0 + e;
         const bool second = r >= c.n;
         v[k] = zero_elem<WIDTH>();
-        if (e < m && (second ? so1 : so0) >= 0) v[k] = load_stream<WIDTH>(src + (second ? b1 : b0) + r);
+        if (e < m && (second ? so1 : so0) >= 0) v[k] = load_stream<WIDTH>(c.src + (second ? b1 : b0) + r * WIDTH);
     }
 #pragma unroll
     for (int k = 0; k < U; k++) {
@@ -239,25 +257,31 @@ __device__ void copy_wide(const CollectArgs& a, const DrawArgs& g, const ColTask
     }
 }
 
+// The windows of a narrow or straddling piece, shared by the workgroup.  One
+// object for every kind of piece, so that the kernel's LDS stays at 2 KB and
+// kCapLds, kShareLds alone set how many workgroups share a CU.
+struct Staged {
+    int64_t off[kThreads];  // source byte offset per window, negative if it reads as zeros
+    int bad;                // a window is invalid
+    int missing;            // a window reads as zeros
+};
+
 template <int WIDTH, int U>
-__device__ void copy_narrow(const CollectArgs& a, const DrawArgs& g, const ColTask& c, int64_t q) {
+__device__ void copy_narrow(const CollectArgs& a, const DrawArgs& g, const ColTask& c, int64_t q, Staged& st) {
     typedef typename Elem<WIDTH>::type V;
-    __shared__ int64_t s_off[kThreads];   // source element offset per window, -1 if invalid
-    __shared__ int s_bad;
     const int64_t b0 = q * c.wpp;
     const int nb = (int)((a.B - b0) < c.wpp ? (a.B - b0) : c.wpp);
-    if (threadIdx.x == 0) s_bad = 0;
+    if (threadIdx.x == 0) st.bad = 0;
     __syncthreads();
     if ((int)threadIdx.x < nb) {
         const int64_t so = window_offset(a, g, c, b0 + threadIdx.x);
-        s_off[threadIdx.x] = so < 0 ? -1 : so / WIDTH;
-        if (so == kBadWindow) s_bad = 1;
+        st.off[threadIdx.x] = so;
+        if (so == kBadWindow) st.bad = 1;
         if (c.draws_out) write_draw(g, b0 + threadIdx.x);
     }
     __syncthreads();
-    if (threadIdx.x == 0 && s_bad) atomicOr(a.status, GEAR_STATUS_BAD_INDEX);
+    if (threadIdx.x == 0 && st.bad) atomicOr(a.status, GEAR_STATUS_BAD_INDEX);
     const uint32_t total = (uint32_t)nb * c.epw;
-    const V* src = reinterpret_cast<const V*>(c.src);
     V* dst = reinterpret_cast<V*>(c.out) + b0 * (int64_t)c.epw;
     V v[U];
 #pragma unroll
@@ -266,8 +290,8 @@ __device__ void copy_narrow(const CollectArgs& a, const DrawArgs& g, const ColTa
         v[k] = zero_elem<WIDTH>();
         if (e < total) {
             const uint32_t w = c.epw == 1 ? e : __umulhi(e, c.magic);
-            const int64_t so = s_off[w];
-            if (so >= 0) v[k] = load_stream<WIDTH>(src + so + (e - w * c.epw));
+            const int64_t so = st.off[w];
+            if (so >= 0) v[k] = load_stream<WIDTH>(c.src + so + (int64_t)(e - w * c.epw) * WIDTH);
         }
     }
 #pragma unroll
@@ -277,21 +301,124 @@ __device__ void copy_narrow(const CollectArgs& a, const DrawArgs& g, const ColTa
     }
 }
 
+// Bytes s .. s + 15 (1 <= s <= 15) of the 32 bytes of a followed by b.
+__device__ __forceinline__ u32x4 join16(u32x4 a, u32x4 b, uint32_t s) {
+    const uint64_t a0 = ((uint64_t)a.y << 32) | a.x, a1 = ((uint64_t)a.w << 32) | a.z;
+    const uint64_t b0 = ((uint64_t)b.y << 32) | b.x, b1 = ((uint64_t)b.w << 32) | b.z;
+    const bool high = s >= 8;
+    const uint64_t x = high ? a1 : a0, y = high ? b0 : a1, z = high ? b1 : b0;
+    const uint32_t bits = (s & 7) * 8;
+    const uint64_t lo = bits ? (x >> bits) | (y << (64 - bits)) : x;
+    const uint64_t hi = bits ? (y >> bits) | (z << (64 - bits)) : y;
+    u32x4 r;
+    r.x = (uint32_t)lo;
+    r.y = (uint32_t)(lo >> 32);
+    r.z = (uint32_t)hi;
+    r.w = (uint32_t)(hi >> 32);
+    return r;
+}
+
+// Piece q of a column whose windows are not whole 16-byte elements: batch
+// bytes [q*P, q*P + m), P = kThreads * U * 16.  A window holds at least 16
+// bytes and a piece touches at most kThreads windows (the host's rule), so an
+// element lies in one window, or covers the last bytes of one and the first of
+// the next: then its two sources are the last 16 bytes of the one and the
+// first 16 of the other, both inside their windows, and the element is 16
+// consecutive bytes of the two together.  All first sources are loaded
+// together; the second ones, on few lanes unless windows are short, follow.
+template <int U>
+__device__ void copy_straddle(const CollectArgs& a, const DrawArgs& g, const ColTask& c, int64_t q, Staged& st) {
+    constexpr int64_t P = (int64_t)kThreads * U * 16;
+    const int64_t o0 = q * P;
+    const int64_t w0 = o0 / c.W;
+    const int64_t total = (int64_t)a.B * c.W;
+    const int32_t m = (int32_t)((total - o0) < P ? (total - o0) : P);
+    const int64_t r0 = o0 - w0 * c.W;
+    // Windows touched; with W >= P the piece may reach into a second one only.
+    const int nw = c.magic ? (int)(((uint32_t)r0 + (uint32_t)m + (uint32_t)c.W - 1) / (uint32_t)c.W)
+                           : (r0 + m > c.W ? 2 : 1);
+    if (threadIdx.x == 0) st.bad = st.missing = 0;
+    __syncthreads();
+    if ((int)threadIdx.x < nw) {
+        const int64_t b = w0 + threadIdx.x;
+        const int64_t so = window_offset(a, g, c, b);
+        st.off[threadIdx.x] = so;
+        if (so < 0) st.missing = 1;
+        if (so == kBadWindow) st.bad = 1;
+        // Every touched window but the first starts inside the piece.
+        if (c.draws_out && (threadIdx.x > 0 || r0 == 0)) write_draw(g, b);
+    }
+    __syncthreads();
+    const bool valid = __builtin_amdgcn_readfirstlane(st.missing) == 0;
+    if (threadIdx.x == 0 && st.bad) atomicOr(a.status, GEAR_STATUS_BAD_INDEX);
+    const int32_t n16 = m / 16;  // whole elements; the batch's last bytes may be fewer
+    u32x4* dst = reinterpret_cast<u32x4*>(c.out + o0);
+    if (n16 > 0) {
+        u32x4 v[U];
+        int64_t at[U];               // offset of the first source, negative for zeros
+        uint32_t win[U], cut[U];     // window; bytes of the first source that are skipped (0: no straddle)
+#pragma unroll
+        for (int k = 0; k < U; k++) {
+            int32_t e = (int32_t)lane_elem<U>(k);
+            e = e < n16 ? e : n16 - 1;
+            const int64_t t = r0 + (int64_t)e * 16;
+            win[k] = c.magic ? __umulhi((uint32_t)t, c.magic) : (t >= c.W ? 1u : 0u);
+            const int64_t r = t - (int64_t)win[k] * c.W;
+            const int64_t last = c.W - 16;
+            cut[k] = r > last ? (uint32_t)(r - last) : 0u;
+            const int64_t so = st.off[win[k]];
+            at[k] = so < 0 ? so : so + (r > last ? last : r);
+        }
+        if (valid) {  // the loads go out unconditionally, all in flight
+#pragma unroll
+            for (int k = 0; k < U; k++) v[k] = load_stream<16>(c.src + at[k]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < U; k++) {
+                v[k] = zero_elem<16>();
+                if (at[k] >= 0) v[k] = load_stream<16>(c.src + at[k]);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < U; k++) {
+            if (cut[k]) {
+                const int64_t so = st.off[win[k] + 1];
+                v[k] = join16(v[k], so >= 0 ? load_stream<16>(c.src + so) : zero_elem<16>(), cut[k]);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < U; k++) {
+            const int32_t e = (int32_t)lane_elem<U>(k);
+            if (e < n16) store_stream<16>(dst + e, v[k]);
+        }
+    }
+    const int32_t t = n16 * 16 + (int32_t)threadIdx.x;
+    if (t < m) {  // fewer than 16 bytes, in the batch's last window
+        const int64_t p = r0 + t;
+        const uint32_t w = c.magic ? __umulhi((uint32_t)p, c.magic) : (p >= c.W ? 1u : 0u);
+        const int64_t so = st.off[w];
+        c.out[o0 + t] = so >= 0 ? c.src[so + (p - (int64_t)w * c.W)] : (uint8_t)0;
+    }
+}
+
 template <int U>
 __global__ __launch_bounds__(kThreads) void collect_kernel(CollectArgs a, DrawArgs g) {
+    __shared__ Staged st;
     const int64_t task = blockIdx.x;
     int j = 0;
     while (j + 1 < a.ncols && a.col[j + 1].task0 <= task) j++;
     const ColTask& c = a.col[j];
     const int64_t q = task - c.task0;
-    if (c.wide) {
+    if (c.layout == kStraddle) {
+        copy_straddle<U>(a, g, c, q, st);
+    } else if (c.layout == kWide) {
         if (c.width == 16) copy_wide<16, U>(a, g, c, q);
         else if (c.width == 4) copy_wide<4, U>(a, g, c, q);
         else copy_wide<1, U>(a, g, c, q);
     } else {
-        if (c.width == 16) copy_narrow<16, U>(a, g, c, q);
-        else if (c.width == 4) copy_narrow<4, U>(a, g, c, q);
-        else copy_narrow<1, U>(a, g, c, q);
+        if (c.width == 16) copy_narrow<16, U>(a, g, c, q, st);
+        else if (c.width == 4) copy_narrow<4, U>(a, g, c, q, st);
+        else copy_narrow<1, U>(a, g, c, q, st);
     }
 }
 
@@ -339,24 +466,23 @@ int launch_collect(Table* t, const int64_t* d_idx, const int32_t* d_start, const
             ct.E = t->elem_bytes[c];
             ct.W = (int64_t)L * ct.E;
             ct.draws_out = draws != nullptr && j == 0;
-            const uintptr_t sa = reinterpret_cast<uintptr_t>(ct.src), oa = reinterpret_cast<uintptr_t>(ct.out);
-            // Window sources lie E bytes apart, or T*E when L = T (every
-            // window then starts at step 0); outputs lie W bytes apart.
-            const int64_t stride = L == t->T ? (int64_t)t->T * ct.E : ct.E;
-            if (stride % 16 == 0 && ct.W % 16 == 0 && sa % 16 == 0 && oa % 16 == 0) ct.width = 16;
-            else if (stride % 4 == 0 && ct.W % 4 == 0 && sa % 4 == 0 && oa % 4 == 0) ct.width = 4;
+            const uintptr_t oa = reinterpret_cast<uintptr_t>(ct.out);
+            const int64_t elems = (int64_t)kThreads * unroll;  // per piece
+            // A straddling piece stages its windows' offsets, one per thread.
+            const bool straddle = oa % 16 == 0 && ct.W % 16 != 0 && ct.W >= 16 && ct.W * (kThreads - 2) >= elems * 16;
+            if (straddle || (oa % 16 == 0 && ct.W % 16 == 0)) ct.width = 16;
+            else if (oa % 4 == 0 && ct.W % 4 == 0) ct.width = 4;
             else ct.width = 1;
-            ct.piece = (int64_t)kThreads * unroll * ct.width;
+            ct.piece = elems * ct.width;
             ct.n = ct.W / ct.width;
             ct.task0 = tasks;
-            if (ct.W >= ct.piece) {
-                ct.wide = 1;
-                ct.wpp = 1;
-                ct.epw = 0;
-                ct.magic = 0;
-                tasks += ((int64_t)B * ct.n + kThreads * unroll - 1) / (kThreads * unroll);
+            ct.layout = straddle ? kStraddle : ct.W >= ct.piece ? kWide : kNarrow;
+            if (ct.layout == kStraddle) {
+                ct.magic = ct.W < ct.piece ? (uint32_t)(((1ull << 32) + ct.W - 1) / ct.W) : 0u;
+                tasks += ((int64_t)B * ct.W + ct.piece - 1) / ct.piece;
+            } else if (ct.layout == kWide) {
+                tasks += ((int64_t)B * ct.n + elems - 1) / elems;
             } else {
-                ct.wide = 0;
                 int64_t wpp = ct.piece / ct.W;
                 if (wpp > kThreads) wpp = kThreads;
                 ct.wpp = (int32_t)wpp;
