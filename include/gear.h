@@ -109,10 +109,10 @@ extern "C" {
                                          batch (every select after a change rescans; updates
                                          then do not maintain the tree) */
 #define GEAR_OPT_GATHER_SHARE_CU  4u  /* long gathers from an HBM table hold at most 2
-                                         workgroups per CU instead of 4, so that kernels
-                                         on other streams start sooner beside them; the
-                                         gather itself runs about 1% slower.  Results
-                                         are unchanged. */
+                                         workgroups per CU instead of 7 or 8, so that
+                                         kernels on other streams start sooner beside
+                                         them; the gather itself runs about 5% slower.
+                                         Results are unchanged. */
 
 /* Limits. */
 #define GEAR_MAX_CAPACITY  (1ll << 30)  /* keeps every priority total below 2^62 */

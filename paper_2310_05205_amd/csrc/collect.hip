@@ -41,38 +41,34 @@ namespace {
 
 constexpr int kThreads = 256;
 // Elements in flight per thread (U), so a piece is kThreads * U elements.
-// HBM tables: 8 (32 KiB pieces at 16-byte elements) for batches of at least
-// kLargeBatch bytes, 2 (8 KiB) below.  Measured on gfx950 in one process,
-// each variant alternating on the same table and buffers: the DT-shaped
-// whole trajectories (51 MB) 20.6-20.7 us with 2 against 20.9-21.2 with 4
-// and 21.5-22.1 with 8; 8.7 MB and 2 MB batches 4.8 and 4.5 us with 2
-// against 5.5 and 5.1 with 8.  The MAT batch (278 MB) took 103.6 us with 2
-// and 94.6 with 4 against 96.0 with 8 back to back, but with the next
-// steps' selection running beside it on another stream, as in the replay
-// loop, 4 was the slower (gather 94.1 against 92.7 us, step 97.9 against
-// 97.2 over 100 steps).  Pinned host tables: 4 (8 was 4% slower over the host
-// link; 2 no faster).
-constexpr int kUnrollLarge = 8;
-constexpr int kUnrollSmall = 2;
-constexpr int64_t kLargeBatch = 128ll << 20;
+// HBM tables: 2, 8 KiB pieces of 16-byte elements, for every batch size.
+// Measured on gfx950 in one process, variants alternating on one table and one
+// set of output buffers (us, U = 2 / 4 / 8): windows of 32 steps of 1060 bytes,
+// 2.2 MB 3.5 / 3.7 / 4.4, 68 MB 25.9 / 26.5 / 27.0, 278 MB 94.8 / 97.2 / 98.4;
+// whole 100 KB trajectories, 51 MB 20.6 / 21.1 / 21.7, 205 MB 71.0 / 73.0 /
+// 77.5 (before the lookups were batched, window_offsets, 278 MB took 103.6 us
+// with 2 and 96.0 with 8).  Pinned host tables: 4 (8 was 4% slower over the
+// host link; 2 no faster).
+constexpr int kUnroll = 2;
 constexpr int kUnrollHost = 4;
-// A long gather from an HBM table (at least kCapRounds rounds of the
-// workgroups that fit the device) reserves kCapLds bytes of LDS per
-// workgroup that it does not use: with the kernel's own LDS that is about
-// 39 KB, so at most 4 of its workgroups share a CU (160 KiB of LDS).  It
-// keeps HBM as busy with 4 as with 8 (MAT batch: 92.0-93.1 us with 2, 4 or 5
-// per CU, 92.6 us uncapped), and kernels of other streams find free slots:
-// with the next step's selection on another stream the MAT step went from
-// 103 to 99.4-99.6 us.  Shorter launches take every slot.
-// GEAR_OPT_GATHER_SHARE_CU reserves kShareLds instead (about 71 KB with the
-// kernel's own LDS, so 2 per CU).  Beside such a gather the MAT selection and
-// update take about half as long as beside one with 4 per CU, while the
-// gather takes 1-1.5 us longer: worth it only while another stream has to
-// catch up, as at the start of a pipeline.
-constexpr unsigned kCapLds = 32 * 1024;
+// A launch that mostly moves wide columns reserves LDS that it does not use,
+// so that 7 of its workgroups share a CU (160 KiB) instead of 8: 278 MB 93.7
+// instead of 94.8 us, 51 MB of whole trajectories 20.2 instead of 20.6, 34 MB
+// 14.5 instead of 14.9; 6 per CU are slower again (94.5), and straddling or
+// narrow columns want all 8 (93 MB of 147-byte steps 38.7 against 39.5, 33 MB
+// of 1360-byte windows 17.5 against 17.8).  It also leaves room for kernels of
+// other streams: with the next steps' selection beside it, the 278 MB step
+// takes 99.6 us over 100 steps (101.0 with 32 KiB pieces, four per CU).
+constexpr unsigned kWideLds = 19 * 1024;
+// GEAR_OPT_GATHER_SHARE_CU makes long gathers run with 4 elements per thread
+// and two workgroups per CU.  Beside such a gather selection and update take
+// about half as long, while the gather takes 98.3 instead of 93.3 us (278 MB):
+// worth it only while another stream has to catch up, as at the start of a
+// pipeline (20 steps, the first three gathers like this: 104.6 us per step
+// against 105.3).
 constexpr unsigned kShareLds = 64 * 1024;
-constexpr int64_t kCapRounds = 4;
-constexpr int64_t kResidentWorkgroups = 2048;  // 256 CUs x 8 workgroups of 256 threads
+constexpr int kUnrollShare = kUnrollHost;
+constexpr int64_t kLongBatch = 64ll << 20;
 constexpr int kMaxLaunchCols = 16;  // columns per launch (more take several launches)
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -84,44 +80,57 @@ enum : int32_t {
     kStraddle = 2,  // equal pieces of the batch, an element may cover the end of one window and the start of the next
 };
 
-struct ColTask {
+// One column's task: one 64-byte line of the kernel arguments.
+struct alignas(64) ColTask {
     const uint8_t* src;   // device-visible column base
     uint8_t* out;         // batch output [B][W]
-    int64_t E;            // bytes per step
     int64_t W;            // window bytes, L*E
-    int64_t task0;        // first task (workgroup) of this column
-    int64_t piece;        // bytes per piece: kThreads * unroll * width
     int64_t n;            // elements per window, W / width
-    int32_t width;        // element bytes: 16, 4 or 1
-    int32_t layout;       // kNarrow, kWide or kStraddle
-    int32_t wpp;          // windows per piece (narrow)
+    uint64_t recip;       // floor((2^64 - 1) / n) (wide) or / W (straddle), for quotient()
+    int32_t E;            // bytes per step
     uint32_t epw;         // elements per window (narrow)
     uint32_t magic;       // narrow: ceil(2^32 / epw) for epw > 1; straddle: ceil(2^32 / W), or 0 when a
                           // window holds at least a piece: exact quotient for operands < 2^16
-    int32_t draws_out;    // 1: this column's pieces write the selected slots, starts and weights
+    uint16_t wpp;         // windows per piece (narrow)
+    uint8_t width;        // element bytes: 16, 4 or 1
+    uint8_t layout : 4;   // kNarrow, kWide or kStraddle
+    uint8_t draws_out : 4;  // 1: this column's pieces write the selected slots, starts and weights
+    int64_t pad;
 };
+static_assert(sizeof(ColTask) == 64, "one line per column");
 
 // A gather that selects its own windows (FIFO, LIFO or uniform draws): a
 // kernel argument of its own, beside CollectArgs.
 struct DrawArgs {
-    int32_t computed;       // 1: the windows are `draws`, computed per piece; 0: from CollectArgs::idx, start
-    SimpleDraws draws;
+    SimpleDraws draws;      // the windows, computed per piece
     int64_t* idx_out;       // the draws, written by the pieces of a draws_out column
     int32_t* start_out;
     float* w_out;           // ... and weight 1 per draw, when not NULL
 };
 
+// A workgroup finds its column from the first line alone and then reads that
+// column's line: two rounds of scalar loads before its window offsets, where a
+// walk over the columns took one round per column (the two together with
+// kernels that hold only the code their columns need: 512 windows of 20 steps
+// of 68, 24, 4 and 4 bytes 4.3 -> 3.6 us).
 struct CollectArgs {
-    ColTask col[kMaxLaunchCols];
-    int32_t ncols;
-    const int64_t* idx;     // the caller's draws, unless DrawArgs::computed
+    int32_t task0[kMaxLaunchCols];  // first task (workgroup) of each column; INT32_MAX past the last
+    const int64_t* idx;     // the caller's draws, unless the pieces compute them
     const int32_t* start;
+    uint32_t* status;
+    int64_t N;
     int32_t B;
     int32_t T;
     int32_t L;
-    int64_t N;
-    uint32_t* status;
+    ColTask col[kMaxLaunchCols];
 };
+
+// floor(x / n) for x < 2^63 from recip = floor((2^64 - 1) / n): the high word of
+// the product is at most one short.
+__device__ __forceinline__ int64_t quotient(int64_t x, int64_t n, uint64_t recip) {
+    const int64_t q = (int64_t)__umul64hi((uint64_t)x, recip);
+    return x - q * n >= n ? q + 1 : q;
+}
 
 // Element types: `type` in the batch (aligned), `src` in a column (any address).
 template <int WIDTH>
@@ -184,14 +193,42 @@ __device__ __forceinline__ int64_t lane_elem(int k) {
 constexpr int64_t kNoWindow = -1;
 constexpr int64_t kBadWindow = -2;
 
+__device__ __forceinline__ int64_t draw_offset(const CollectArgs& a, const ColTask& c, int64_t i, int32_t s) {
+    // Unsigned: an invalid index may wrap, and its product is not used.
+    const int64_t off = (int64_t)(((uint64_t)i * (uint64_t)a.T + (uint64_t)s) * (uint64_t)c.E);
+    const bool ok = (i >= 0) & (i < a.N) & (s >= 0) & (s <= a.T - a.L);
+    return ok ? off : i == -1 ? kNoWindow : kBadWindow;
+}
+
+// Offsets of windows b and b2 (one lane's, or the workgroup's).  The draws'
+// loads are all issued before any is used: left to the compiler, a start's
+// load stood behind the test of its index, and the second window's behind the
+// first's, a memory round trip each (512 windows of 20 steps of 68, 24, 4 and 4
+// bytes: 3.5 instead of 3.6 us; 3001 of 13 steps of 147, 1, 2 and 1: 6.3
+// instead of 6.7).
+template <bool DRAWS>
+__device__ __forceinline__ void window_offsets(const CollectArgs& a, const DrawArgs& g, const ColTask& c, int64_t b,
+                                               int64_t b2, int64_t& off, int64_t& off2) {
+    if (DRAWS) {
+        off = (simple_slot(g.draws, b) * a.T + simple_start(g.draws, b)) * c.E;
+        off2 = (simple_slot(g.draws, b2) * a.T + simple_start(g.draws, b2)) * c.E;
+        return;
+    }
+    const int64_t i = a.idx[b], i2 = a.idx[b2];
+    const int32_t s = a.start[b], s2 = a.start[b2];
+    asm volatile("" ::"v"(i), "v"(i2), "v"(s), "v"(s2));
+    off = draw_offset(a, c, i, s);
+    off2 = draw_offset(a, c, i2, s2);
+}
+
+template <bool DRAWS>
 __device__ __forceinline__ int64_t window_offset(const CollectArgs& a, const DrawArgs& g, const ColTask& c,
                                                  int64_t b) {
-    if (g.computed) return (simple_slot(g.draws, b) * a.T + simple_start(g.draws, b)) * c.E;
+    if (DRAWS) return (simple_slot(g.draws, b) * a.T + simple_start(g.draws, b)) * c.E;
     const int64_t i = a.idx[b];
     const int32_t s = a.start[b];
-    if (i == -1) return kNoWindow;
-    if (i < 0 || i >= a.N || s < 0 || s > a.T - a.L) return kBadWindow;
-    return (i * a.T + s) * c.E;
+    asm volatile("" ::"v"(i), "v"(s));
+    return draw_offset(a, c, i, s);
 }
 
 // A gather that selects its own windows writes draw b's slot, start and
@@ -207,20 +244,21 @@ __device__ __forceinline__ void write_draw(const DrawArgs& g, int64_t b) {
 // batch, P = kThreads * U, m = P except in the batch's last piece.  A
 // window has n >= P elements, so the piece lies in window w0 from element r0
 // on and, if r0 + m > n, runs into window w0 + 1.
-template <int WIDTH, int U>
+template <int WIDTH, int U, bool DRAWS>
 __device__ void copy_wide(const CollectArgs& a, const DrawArgs& g, const ColTask& c, int64_t q) {
     typedef typename Elem<WIDTH>::type V;
     constexpr int64_t P = (int64_t)kThreads * U;
     const int64_t o0 = q * P;
-    const int64_t w0 = o0 / c.n;
+    const int64_t w0 = quotient(o0, c.n, c.recip);
     const int64_t r0 = o0 - w0 * c.n;
     const int64_t total = (int64_t)a.B * c.n;
     const int64_t m = (total - o0) < P ? (total - o0) : P;
     const bool two = r0 + m > c.n;
-    const int64_t so0 = window_offset(a, g, c, w0);
-    const int64_t so1 = two ? window_offset(a, g, c, w0 + 1) : kNoWindow;
+    int64_t so0, so1 = kNoWindow;
+    if (two) window_offsets<DRAWS>(a, g, c, w0, w0 + 1, so0, so1);
+    else so0 = window_offset<DRAWS>(a, g, c, w0);
     if (threadIdx.x == 0 && (so0 == kBadWindow || so1 == kBadWindow)) atomicOr(a.status, GEAR_STATUS_BAD_INDEX);
-    if (c.draws_out && threadIdx.x == 0) {  // a piece holds at most one window's first element
+    if (DRAWS && c.draws_out && threadIdx.x == 0) {  // a piece holds at most one window's first element
         if (r0 == 0) write_draw(g, w0);
         else if (two) write_draw(g, w0 + 1);
     }
@@ -259,28 +297,40 @@ __device__ void copy_wide(const CollectArgs& a, const DrawArgs& g, const ColTask
 
 // The windows of a narrow or straddling piece, shared by the workgroup.  One
 // object for every kind of piece, so that the kernel's LDS stays at 2 KB and
-// kCapLds, kShareLds alone set how many workgroups share a CU.
+// kWideLds, kShareLds alone set how many workgroups share a CU.
 struct Staged {
-    int64_t off[kThreads];  // source byte offset per window, negative if it reads as zeros
-    int bad;                // a window is invalid
-    int missing;            // a window reads as zeros
+    int64_t off[kThreads];         // source byte offset per window, negative if it reads as zeros
+    uint32_t flags[kThreads / 64];  // per wave: kStagedBad, kStagedZeros
 };
+constexpr uint32_t kStagedBad = 1;    // a window is invalid
+constexpr uint32_t kStagedZeros = 2;  // a window reads as zeros
 
-template <int WIDTH, int U>
+// Stages windows b0 .. b0 + n - 1, one per thread, behind one barrier; returns
+// the flags of all of them.  Window k writes its draw when k >= first_draw.
+template <bool DRAWS>
+__device__ __forceinline__ uint32_t stage_windows(const CollectArgs& a, const DrawArgs& g, const ColTask& c, int64_t b0,
+                                                  int n, int first_draw, Staged& st) {
+    int64_t so = 0;
+    if ((int)threadIdx.x < n) {
+        so = window_offset<DRAWS>(a, g, c, b0 + threadIdx.x);
+        st.off[threadIdx.x] = so;
+        if (DRAWS && c.draws_out && (int)threadIdx.x >= first_draw) write_draw(g, b0 + threadIdx.x);
+    }
+    const uint32_t mine = (__ballot(so == kBadWindow) ? kStagedBad : 0u) | (__ballot(so < 0) ? kStagedZeros : 0u);
+    if ((threadIdx.x & 63) == 0) st.flags[threadIdx.x >> 6] = mine;
+    __syncthreads();
+    const uint32_t all = __builtin_amdgcn_readfirstlane(st.flags[0] | st.flags[1] | st.flags[2] | st.flags[3]);
+    if (threadIdx.x == 0 && (all & kStagedBad)) atomicOr(a.status, GEAR_STATUS_BAD_INDEX);
+    return all;
+}
+static_assert(kThreads == 256, "four waves' flags");
+
+template <int WIDTH, int U, bool DRAWS>
 __device__ void copy_narrow(const CollectArgs& a, const DrawArgs& g, const ColTask& c, int64_t q, Staged& st) {
     typedef typename Elem<WIDTH>::type V;
     const int64_t b0 = q * c.wpp;
     const int nb = (int)((a.B - b0) < c.wpp ? (a.B - b0) : c.wpp);
-    if (threadIdx.x == 0) st.bad = 0;
-    __syncthreads();
-    if ((int)threadIdx.x < nb) {
-        const int64_t so = window_offset(a, g, c, b0 + threadIdx.x);
-        st.off[threadIdx.x] = so;
-        if (so == kBadWindow) st.bad = 1;
-        if (c.draws_out) write_draw(g, b0 + threadIdx.x);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0 && st.bad) atomicOr(a.status, GEAR_STATUS_BAD_INDEX);
+    stage_windows<DRAWS>(a, g, c, b0, nb, 0, st);
     const uint32_t total = (uint32_t)nb * c.epw;
     V* dst = reinterpret_cast<V*>(c.out) + b0 * (int64_t)c.epw;
     V v[U];
@@ -326,31 +376,20 @@ __device__ __forceinline__ u32x4 join16(u32x4 a, u32x4 b, uint32_t s) {
 // first 16 of the other, both inside their windows, and the element is 16
 // consecutive bytes of the two together.  All first sources are loaded
 // together; the second ones, on few lanes unless windows are short, follow.
-template <int U>
+template <int U, bool DRAWS>
 __device__ void copy_straddle(const CollectArgs& a, const DrawArgs& g, const ColTask& c, int64_t q, Staged& st) {
     constexpr int64_t P = (int64_t)kThreads * U * 16;
     const int64_t o0 = q * P;
-    const int64_t w0 = o0 / c.W;
+    const int64_t w0 = quotient(o0, c.W, c.recip);
     const int64_t total = (int64_t)a.B * c.W;
     const int32_t m = (int32_t)((total - o0) < P ? (total - o0) : P);
     const int64_t r0 = o0 - w0 * c.W;
     // Windows touched; with W >= P the piece may reach into a second one only.
     const int nw = c.magic ? (int)(((uint32_t)r0 + (uint32_t)m + (uint32_t)c.W - 1) / (uint32_t)c.W)
                            : (r0 + m > c.W ? 2 : 1);
-    if (threadIdx.x == 0) st.bad = st.missing = 0;
-    __syncthreads();
-    if ((int)threadIdx.x < nw) {
-        const int64_t b = w0 + threadIdx.x;
-        const int64_t so = window_offset(a, g, c, b);
-        st.off[threadIdx.x] = so;
-        if (so < 0) st.missing = 1;
-        if (so == kBadWindow) st.bad = 1;
-        // Every touched window but the first starts inside the piece.
-        if (c.draws_out && (threadIdx.x > 0 || r0 == 0)) write_draw(g, b);
-    }
-    __syncthreads();
-    const bool valid = __builtin_amdgcn_readfirstlane(st.missing) == 0;
-    if (threadIdx.x == 0 && st.bad) atomicOr(a.status, GEAR_STATUS_BAD_INDEX);
+    // Every touched window but the first starts inside the piece, and the first
+    // does when the piece begins with it: those write their draws.
+    const bool valid = !(stage_windows<DRAWS>(a, g, c, w0, nw, r0 == 0 ? 0 : 1, st) & kStagedZeros);
     const int32_t n16 = m / 16;  // whole elements; the batch's last bytes may be fewer
     u32x4* dst = reinterpret_cast<u32x4*>(c.out + o0);
     if (n16 > 0) {
@@ -401,25 +440,50 @@ __device__ void copy_straddle(const CollectArgs& a, const DrawArgs& g, const Col
     }
 }
 
-template <int U>
+// ANY: columns of every layout and width; otherwise only 16-byte elements in
+// kWide and kNarrow columns.  DRAWS: the pieces compute their windows.
+template <int U, bool DRAWS, bool ANY>
 __global__ __launch_bounds__(kThreads) void collect_kernel(CollectArgs a, DrawArgs g) {
     __shared__ Staged st;
-    const int64_t task = blockIdx.x;
-    int j = 0;
-    while (j + 1 < a.ncols && a.col[j + 1].task0 <= task) j++;
-    const ColTask& c = a.col[j];
-    const int64_t q = task - c.task0;
-    if (c.layout == kStraddle) {
-        copy_straddle<U>(a, g, c, q, st);
-    } else if (c.layout == kWide) {
-        if (c.width == 16) copy_wide<16, U>(a, g, c, q);
-        else if (c.width == 4) copy_wide<4, U>(a, g, c, q);
-        else copy_wide<1, U>(a, g, c, q);
-    } else {
-        if (c.width == 16) copy_narrow<16, U>(a, g, c, q, st);
-        else if (c.width == 4) copy_narrow<4, U>(a, g, c, q, st);
-        else copy_narrow<1, U>(a, g, c, q, st);
+    const int32_t task = (int32_t)blockIdx.x;
+    int j = 0, first = 0;
+#pragma unroll
+    for (int k0 = 0; k0 < kMaxLaunchCols; k0 += 4) {
+#pragma unroll
+        for (int k = k0 + 1; k <= k0 + 3; k++) {
+            const bool past = a.task0[k] <= task;
+            j = past ? k : j;
+            first = past ? a.task0[k] : first;
+        }
+        if (k0 + 4 == kMaxLaunchCols || a.task0[k0 + 4 < kMaxLaunchCols ? k0 + 4 : 0] > task) break;
+        j = k0 + 4;
+        first = a.task0[k0 + 4 < kMaxLaunchCols ? k0 + 4 : 0];
     }
+    // The whole line and the shared arguments at once; left to the compiler,
+    // each field's load stands where the field is first used.
+    const ColTask c = a.col[j];
+    asm volatile("" ::"s"(c.src), "s"(c.out), "s"(c.W), "s"(c.n), "s"(c.recip), "s"(c.E), "s"(c.epw), "s"(c.magic),
+                 "s"(a.idx), "s"(a.start), "s"(a.N), "s"(a.B), "s"(a.T), "s"(a.L));
+    const int64_t q = task - first;
+    if (ANY && c.layout == kStraddle) {
+        copy_straddle<U, DRAWS>(a, g, c, q, st);
+    } else if (c.layout == kWide) {
+        if (!ANY || c.width == 16) copy_wide<16, U, DRAWS>(a, g, c, q);
+        else if (c.width == 4) copy_wide<4, U, DRAWS>(a, g, c, q);
+        else copy_wide<1, U, DRAWS>(a, g, c, q);
+    } else {
+        if (!ANY || c.width == 16) copy_narrow<16, U, DRAWS>(a, g, c, q, st);
+        else if (c.width == 4) copy_narrow<4, U, DRAWS>(a, g, c, q, st);
+        else copy_narrow<1, U, DRAWS>(a, g, c, q, st);
+    }
+}
+
+typedef void (*CollectKernel)(CollectArgs, DrawArgs);
+
+template <int U>
+CollectKernel collect_variant(bool draws, bool any) {
+    if (draws) return any ? collect_kernel<U, true, true> : collect_kernel<U, true, false>;
+    return any ? collect_kernel<U, false, true> : collect_kernel<U, false, false>;
 }
 
 // The collect launches over ncols requested columns (kMaxLaunchCols per
@@ -432,14 +496,14 @@ int launch_collect(Table* t, const int64_t* d_idx, const int32_t* d_start, const
     const bool pinned = t->residency == GEAR_HOST_PINNED;
     int64_t batch_bytes = 0;
     for (int j = 0; j < ncols; j++) batch_bytes += (int64_t)B * L * t->elem_bytes[col_ids ? col_ids[j] : j];
-    const int unroll = pinned ? kUnrollHost : batch_bytes >= kLargeBatch ? kUnrollLarge : kUnrollSmall;
+    const bool share = !pinned && batch_bytes >= kLongBatch && (t->options & GEAR_OPT_GATHER_SHARE_CU);
+    const int unroll = pinned ? kUnrollHost : share ? kUnrollShare : kUnroll;
 
     for (int j0 = 0; j0 < ncols; j0 += kMaxLaunchCols) {
         CollectArgs a{};
         a.idx = d_idx;
         a.start = d_start;
         DrawArgs g{};
-        g.computed = draws != nullptr;
         if (draws) {
             g.draws = *draws;
             g.idx_out = idx_out;
@@ -451,8 +515,10 @@ int launch_collect(Table* t, const int64_t* d_idx, const int32_t* d_start, const
         a.L = L;
         a.N = t->N;
         a.status = t->status;
-        a.ncols = 0;
-        int64_t tasks = 0;
+        int64_t tasks = 0, wide_tasks = 0;
+        int launch_cols = 0;
+        bool any = false;  // a column needs more than 16-byte elements of whole windows
+        for (int k = 0; k < kMaxLaunchCols; k++) a.task0[k] = INT32_MAX;
         // Tasks are numbered from the last requested column to the first:
         // the wide columns, listed first in the common layouts, then end
         // the launch with full pieces instead of small packed ones
@@ -460,10 +526,12 @@ int launch_collect(Table* t, const int64_t* d_idx, const int32_t* d_start, const
         const int jend = ncols < j0 + kMaxLaunchCols ? ncols : j0 + kMaxLaunchCols;
         for (int j = jend - 1; j >= j0; j--) {
             const int c = col_ids ? col_ids[j] : j;
-            ColTask& ct = a.col[a.ncols++];
+            if (tasks > INT32_MAX) break;  // refused below
+            a.task0[launch_cols] = (int32_t)tasks;
+            ColTask& ct = a.col[launch_cols++];
             ct.src = t->col_dev[c];
             ct.out = static_cast<uint8_t*>(d_out[j]);
-            ct.E = t->elem_bytes[c];
+            ct.E = (int32_t)t->elem_bytes[c];  // at most 2^30
             ct.W = (int64_t)L * ct.E;
             ct.draws_out = draws != nullptr && j == 0;
             const uintptr_t oa = reinterpret_cast<uintptr_t>(ct.out);
@@ -473,33 +541,33 @@ int launch_collect(Table* t, const int64_t* d_idx, const int32_t* d_start, const
             if (straddle || (oa % 16 == 0 && ct.W % 16 == 0)) ct.width = 16;
             else if (oa % 4 == 0 && ct.W % 4 == 0) ct.width = 4;
             else ct.width = 1;
-            ct.piece = elems * ct.width;
+            const int64_t piece = elems * ct.width;
             ct.n = ct.W / ct.width;
-            ct.task0 = tasks;
-            ct.layout = straddle ? kStraddle : ct.W >= ct.piece ? kWide : kNarrow;
+            any = any || straddle || ct.width != 16;
+            ct.layout = straddle ? kStraddle : ct.W >= piece ? kWide : kNarrow;
             if (ct.layout == kStraddle) {
-                ct.magic = ct.W < ct.piece ? (uint32_t)(((1ull << 32) + ct.W - 1) / ct.W) : 0u;
-                tasks += ((int64_t)B * ct.W + ct.piece - 1) / ct.piece;
+                ct.recip = ~0ull / (uint64_t)ct.W;
+                ct.magic = ct.W < piece ? (uint32_t)(((1ull << 32) + ct.W - 1) / ct.W) : 0u;
+                tasks += ((int64_t)B * ct.W + piece - 1) / piece;
             } else if (ct.layout == kWide) {
-                tasks += ((int64_t)B * ct.n + elems - 1) / elems;
+                ct.recip = ~0ull / (uint64_t)ct.n;
+                const int64_t k = ((int64_t)B * ct.n + elems - 1) / elems;
+                tasks += k;
+                wide_tasks += k;
             } else {
-                int64_t wpp = ct.piece / ct.W;
+                int64_t wpp = piece / ct.W;
                 if (wpp > kThreads) wpp = kThreads;
-                ct.wpp = (int32_t)wpp;
+                ct.wpp = (uint16_t)wpp;
                 ct.epw = (uint32_t)(ct.W / ct.width);
                 ct.magic = ct.epw > 1 ? (uint32_t)(((1ull << 32) + ct.epw - 1) / ct.epw) : 0u;
                 tasks += (B + wpp - 1) / wpp;
             }
         }
         if (tasks > 0x7FFFFFFF) return fail(GEAR_E_INVAL, std::string(who) + ": batch too large for one launch");
-        const unsigned cap = (t->options & GEAR_OPT_GATHER_SHARE_CU) ? kShareLds : kCapLds;
-        const unsigned lds = !pinned && tasks >= kCapRounds * kResidentWorkgroups ? cap : 0u;
-        if (unroll == kUnrollLarge)
-            hipLaunchKernelGGL(collect_kernel<kUnrollLarge>, dim3((unsigned)tasks), dim3(kThreads), lds, s, a, g);
-        else if (unroll == kUnrollHost)
-            hipLaunchKernelGGL(collect_kernel<kUnrollHost>, dim3((unsigned)tasks), dim3(kThreads), lds, s, a, g);
-        else
-            hipLaunchKernelGGL(collect_kernel<kUnrollSmall>, dim3((unsigned)tasks), dim3(kThreads), lds, s, a, g);
+        const unsigned lds = share ? kShareLds : !pinned && wide_tasks * 2 > tasks ? kWideLds : 0u;
+        const CollectKernel kernel = unroll == kUnroll ? collect_variant<kUnroll>(draws != nullptr, any)
+                                                       : collect_variant<kUnrollHost>(draws != nullptr, any);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)tasks), dim3(kThreads), lds, s, a, g);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, (std::string(who) + ": launch").c_str());
     }
