@@ -12,18 +12,22 @@
 
 namespace gear {
 
-// Priority scan geometry.  A tile is 256 priorities: one wave64, four per
-// lane, one 16-byte load per lane.  A chunk (one workgroup of the scan) is
-// 32 tiles.  Selection walks a 256-ary sum tree: level 0 holds the sum of
-// every tile, level l the sum of every 256^l tiles; the top level has at most
-// 256 nodes.
+// Priority scan geometry.  A tile is 256 priorities, a chunk (one workgroup
+// of the scan) 16 tiles, or 64 above kSmallChunksMax priorities.  Selection
+// walks a sum tree: level 0 holds the sum of every tile, level 1 the sum of
+// every chunk, level 2 (only when there are more than kTopMax chunks, N > 2^24)
+// the sum of every 256 chunks.  The search keeps the prefixes of the highest
+// level, at most kTopMax nodes, in LDS.
 constexpr int kTile = 256;
-constexpr int kTilesPerChunk = 32;
-constexpr int kFanout = 256;
-constexpr int kMaxLevels = 6;
+constexpr int kTopMax = 1024;
+constexpr int kFanout = 256;   // chunks per level-2 node
+constexpr int kMaxLevels = 3;
+constexpr int kSmallChunk = 16, kLargeChunk = 64;  // tiles per chunk
+constexpr int64_t kSmallChunksMax = (int64_t)kTopMax * kSmallChunk * kTile;  // 2^22
+inline int tiles_per_chunk(int64_t N) { return N <= kSmallChunksMax ? kSmallChunk : kLargeChunk; }
 // The search runs at most this many workgroups; each leaves the smallest
 // priority its draws selected in one slot of Table::wg_min.
-constexpr int kSearchMaxGrid = 2048;
+constexpr int kSearchMaxGrid = 1024;
 constexpr int64_t kSmallN = GEAR_SMALL_SELECT_MAX_N;  // tables this small select in one launch (prefix in LDS)
 constexpr int32_t kSmallMaxB = GEAR_SMALL_SELECT_MAX_B;  // ... for batches up to this size
 // TopK: at most this many workgroups per digit pass.
@@ -62,10 +66,11 @@ struct Table {
 
     // Scan / search state.
     int64_t ntiles = 0, nchunks = 0;
-    int nlevels = 0;                  // levels of the sum tree (level 0 = per tile)
+    int nlevels = 0;                  // levels of the sum tree, 2 or 3
     int64_t level_size[kMaxLevels] = {};
     uint64_t* tile_sums = nullptr;    // level 0, rewritten by every scan
-    uint64_t* upper[2][kMaxLevels] = {};  // levels >= 1, two copies: a scan adds into
+    uint64_t* chunk_sums = nullptr;   // level 1, rewritten by every scan
+    uint64_t* upper[2] = {};          // level 2 (if any), two copies: a scan adds into
                                       // one and zeroes the other for the next scan
     int tree_parity = 0;              // copy filled by the last scan
     uint32_t* wg_min = nullptr;       // [kSearchMaxGrid] per-workgroup minimum selected priority

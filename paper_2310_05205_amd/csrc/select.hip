@@ -6,22 +6,21 @@
 // waits on another:
 //
 //   scan_kernel    one pass over the priorities.  A workgroup reduces a
-//                  chunk of 32 tiles of 256 priorities, writes each tile's
-//                  sum (level 0 of a 256-ary sum tree) and adds the chunk's
-//                  sum into the one node of every higher level that covers
-//                  it (at most 8 chunks share a level-1 node).  The top
-//                  level has at most 256 nodes.
-//   search_kernel  one wave per draw: the wave loads the top level (four
-//                  nodes per lane), forms its inclusive prefix with a wave
-//                  scan in registers (the total is S), draws r =
-//                  floor(u*S/2^64), then descends: at each level it scans
-//                  the 256 children of the chosen node in registers, counts
-//                  the children whose inclusive prefix is <= r (ballot +
-//                  popcount), takes the next one and subtracts the prefix
-//                  before it from r; at the leaves it does the same over the
-//                  chosen tile's 256 priorities.  The index found is the
-//                  smallest i with C_i > r for the inclusive prefix C over
-//                  all priorities: the binary-search answer.
+//                  chunk of 16 tiles of 256 priorities (64 above 2^22
+//                  priorities) and writes each tile's sum and the chunk's
+//                  (levels 0 and 1 of the sum tree); above 2^24 priorities it
+//                  also adds the chunk's sum into the level-2 node that covers
+//                  it.
+//   search_kernel  16 lanes (one DPP row) per draw.  Each workgroup forms the
+//                  inclusive prefix of the highest level, at most 1024 nodes,
+//                  in LDS (its last entry is the total S); a draw r =
+//                  floor(u*S/2^64) finds its node there by probing 16 evenly
+//                  spaced entries at a time, then its tile among the chunk's
+//                  (one or four sums per lane, a row scan) and its slot among the
+//                  tile's 256 priorities (16 per lane), r reduced by the prefix
+//                  before each choice.  The index found is the smallest i with
+//                  C_i > r for the inclusive prefix C over all priorities: the
+//                  binary-search answer.
 //
 // Small tables (N <= kSmallN, B <= kSmallMaxB, sum tree not kept across
 // updates) take one launch instead: small_select_kernel, one workgroup,
@@ -55,29 +54,27 @@ inline Levels with_top(Levels lv) {
     return lv;
 }
 
-// Inclusive prefix of 256 values held four per lane (lane l holds values
-// 4l..4l+3): c0..c3 receive the prefix at this lane's four positions.
-__device__ inline void wave_prefix4(uint64_t v0, uint64_t v1, uint64_t v2, uint64_t v3, uint64_t& c0,
-                                    uint64_t& c1, uint64_t& c2, uint64_t& c3) {
-    const uint64_t part = v0 + v1 + v2 + v3;
-    const uint64_t excl = wave_inclusive_scan(part) - part;
-    c0 = excl + v0;
-    c1 = c0 + v1;
-    c2 = c1 + v2;
-    c3 = c2 + v3;
+// Inclusive prefix within each row of 16 lanes.
+__device__ __forceinline__ uint64_t row_inclusive_scan(uint64_t v) {
+    v += dpp_u64<0x111, 0xf>(v);  // row_shr:1
+    v += dpp_u64<0x112, 0xf>(v);  // row_shr:2
+    v += dpp_u64<0x114, 0xf>(v);  // row_shr:4
+    v += dpp_u64<0x118, 0xf>(v);  // row_shr:8
+    return v;
 }
 
-// Among 256 positions whose inclusive prefixes are c0..c3 (four per lane),
-// the number whose prefix is <= r, i.e. the position of the first prefix
-// greater than r; r is reduced by the prefix before that position.
-__device__ inline int pick_child(uint64_t c0, uint64_t c1, uint64_t c2, uint64_t c3, uint64_t& r) {
-    const int cnt = __popcll(__ballot(c0 <= r)) + __popcll(__ballot(c1 <= r)) + __popcll(__ballot(c2 <= r)) +
-                    __popcll(__ballot(c3 <= r));
-    if (cnt > 0) {
-        const int k = cnt - 1;
-        r -= read_lane(pick4(c0, c1, c2, c3, k & 3), k >> 2);
-    }
-    return cnt;
+// Number of lanes of this lane's row for which `b` holds.
+__device__ __forceinline__ int row_count(bool b) {
+    return __popc((uint32_t)(__ballot(b) >> (threadIdx.x & 48)) & 0xFFFFu);
+}
+
+// Among four values, the number whose inclusive prefix is <= r (0 .. 3; the
+// fourth is the answer when no earlier one is) and the prefix before it.
+__device__ __forceinline__ int pick_of4(uint64_t v0, uint64_t v1, uint64_t v2, uint64_t r, uint64_t& before) {
+    const uint64_t c1 = v0 + v1, c2 = c1 + v2;
+    const bool b0 = v0 <= r, b1 = c1 <= r, b2 = c2 <= r;
+    before = b2 ? c2 : b1 ? c1 : b0 ? v0 : 0;
+    return (int)b0 + (int)b1 + (int)b2;
 }
 
 __device__ inline void load4_u64(const uint64_t* __restrict__ a, int64_t n, int64_t e, uint64_t& v0, uint64_t& v1,
@@ -107,36 +104,50 @@ __device__ inline void load4_u32(const uint32_t* __restrict__ a, int64_t n, int6
     }
 }
 
-// `upper` holds the levels >= 1 this scan adds into; `clear` the other copy
-// of those levels, which this scan zeroes for the next one (each node is
-// zeroed by the chunk that starts it).
-// kMin: also write the chunk's smallest non-zero priority (only the
-// global IS normalisation needs it; the plain scan stays minimal).
-template <bool kMin>
-__global__ __launch_bounds__(256) void scan_kernel(const uint32_t* __restrict__ prio, int64_t N, Levels upper,
-                                                   Levels clear, uint64_t* __restrict__ tile_sums, int64_t ntiles,
-                                                   uint32_t* __restrict__ chunk_min) {
-    __shared__ uint64_t tile_sum[kTilesPerChunk];
-    __shared__ uint32_t wave_min[4];
+// Every wave reduces four tiles, four 16-byte loads per lane, all issued before
+// any is used: 256 threads per chunk of 16 tiles, so that a table of half a
+// million priorities is spread over 123 CUs, and 1024 per chunk of 64.
+// Against 256 threads per chunk of 32 tiles and an atomic per chunk: 500000
+// priorities behind an update 4.3 -> 3.1 us, 2^22 6.8 -> 5.3.
+//
+// `upper` is the level-2 copy this scan adds into, or NULL; `clear` the other
+// copy, which this scan zeroes for the next one (each node is zeroed by the
+// chunk that starts it).  kMin: also write the chunk's smallest non-zero
+// priority (only the global IS normalisation needs it).
+template <bool kMin, int kTiles>
+__global__ __launch_bounds__(kTiles * 16) void scan_kernel(const uint32_t* __restrict__ prio, int64_t N,
+                                                           uint64_t* __restrict__ upper,
+                                                           uint64_t* __restrict__ clear,
+                                                           uint64_t* __restrict__ tile_sums, int64_t ntiles,
+                                                           uint64_t* __restrict__ chunk_sums,
+                                                           uint32_t* __restrict__ chunk_min) {
+    constexpr int kScanWaves = kTiles / 4;
+    __shared__ uint64_t tile_sum[kTiles];
+    __shared__ uint32_t wave_min[kScanWaves];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int64_t chunk = blockIdx.x;
-    constexpr int kTilesPerWave = kTilesPerChunk / 4;
+    constexpr int kTilesPerWave = 4;
 
-    // Wave w owns tiles 8w .. 8w+7 of the chunk: eight 16-byte loads per
-    // lane, all issued before any is used.
+    const int64_t tile0 = chunk * kTiles + wave * kTilesPerWave;
     uint32_t x[kTilesPerWave][4];
+    if ((tile0 + kTilesPerWave) * kTile <= N) {  // the same branch for the whole wave
 #pragma unroll
-    for (int q = 0; q < kTilesPerWave; q++)
-        load4_u32(prio, N, (chunk * kTilesPerChunk + wave * kTilesPerWave + q) * kTile + lane * 4, x[q][0], x[q][1],
-                  x[q][2], x[q][3]);
+        for (int q = 0; q < kTilesPerWave; q++) {
+            const uint4 v = *reinterpret_cast<const uint4*>(prio + (tile0 + q) * kTile + lane * 4);
+            x[q][0] = v.x; x[q][1] = v.y; x[q][2] = v.z; x[q][3] = v.w;
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < kTilesPerWave; q++)
+            load4_u32(prio, N, (tile0 + q) * kTile + lane * 4, x[q][0], x[q][1], x[q][2], x[q][3]);
+    }
 #pragma unroll
     for (int q = 0; q < kTilesPerWave; q++) {
         const uint64_t s = wave_sum((uint64_t)x[q][0] + x[q][1] + x[q][2] + x[q][3]);
-        const int64_t gt = chunk * kTilesPerChunk + wave * kTilesPerWave + q;
         if (lane == 0) {
             tile_sum[wave * kTilesPerWave + q] = s;
-            if (gt < ntiles) tile_sums[gt] = s;
+            if (tile0 + q < ntiles) tile_sums[tile0 + q] = s;
         }
     }
     if (kMin) {
@@ -157,20 +168,25 @@ __global__ __launch_bounds__(256) void scan_kernel(const uint32_t* __restrict__ 
     if (wave != 0) return;
     if (kMin && lane == 0) {
         uint32_t cm = wave_min[0];
-        for (int k = 1; k < 4; k++) cm = wave_min[k] < cm ? wave_min[k] : cm;
+        for (int k = 1; k < kScanWaves; k++) cm = wave_min[k] < cm ? wave_min[k] : cm;
         chunk_min[chunk] = cm;
     }
-    const uint64_t chunk_sum = wave_sum(lane < kTilesPerChunk ? tile_sum[lane] : 0);
-    // Lane l - 1 handles level l (>= 1).
-    const int l = lane + 1;
-    if (l < upper.nlevels) {
-        int64_t tiles_per_node = kFanout;
-        for (int k = 1; k < l; k++) tiles_per_node *= kFanout;
-        const int64_t first_tile = chunk * kTilesPerChunk;
-        const int64_t node = first_tile / tiles_per_node;
-        if (chunk_sum != 0) atomicAdd(reinterpret_cast<unsigned long long*>(upper.level[l] + node), chunk_sum);
-        if (first_tile % tiles_per_node == 0) clear.level[l][node] = 0;
+    const uint64_t chunk_sum = wave_sum(lane < kTiles ? tile_sum[lane] : 0);
+    if (lane != 0) return;
+    chunk_sums[chunk] = chunk_sum;
+    if (upper != nullptr) {
+        if (chunk_sum != 0) atomicAdd(reinterpret_cast<unsigned long long*>(upper + chunk / kFanout), chunk_sum);
+        if (chunk % kFanout == 0) clear[chunk / kFanout] = 0;
     }
+}
+
+typedef void (*ScanKernel)(const uint32_t*, int64_t, uint64_t*, uint64_t*, uint64_t*, int64_t, uint64_t*, uint32_t*);
+
+unsigned scan_threads(int64_t N) { return (unsigned)tiles_per_chunk(N) * 16; }
+
+ScanKernel scan_variant(bool min, int64_t N) {
+    if (tiles_per_chunk(N) == kSmallChunk) return min ? scan_kernel<true, kSmallChunk> : scan_kernel<false, kSmallChunk>;
+    return min ? scan_kernel<true, kLargeChunk> : scan_kernel<false, kLargeChunk>;
 }
 
 // One GPU's share of a selection over G shards (the table is shard g).
@@ -181,23 +197,49 @@ struct Shard {
     int64_t base;            // added to the local slot of an owned draw
 };
 
-template <bool kShard>
-__global__ __launch_bounds__(256) void search_kernel(const uint32_t* __restrict__ prio, int64_t N, Levels lv,
-                                                     int32_t B, uint64_t span, uint64_t seed, int want_min,
-                                                     Shard sh, uint32_t* __restrict__ wg_min, uint32_t* status,
-                                                     int64_t* __restrict__ idx, int32_t* __restrict__ start,
-                                                     uint32_t* __restrict__ sel_prio) {
-    __shared__ uint32_t s_min[4];
-    const int lane = threadIdx.x & 63;
-    const int64_t wave_id = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    const int top = lv.nlevels - 1;
+// One row of 16 lanes per draw, 16 draws per workgroup.  The search is a chain
+// of three dependent loads (highest level, tile sums, priorities); with a whole
+// wave per draw and a 64-lane scan at each level it was bound by instruction
+// issue instead (8192 waves of about 300): 8192 draws over 2^22 priorities 7.2
+// -> 5.7 us, 32768 draws with weights and update 32.5 -> 23.3 us.
+constexpr int kSearchThreads = 256;
+constexpr int kSearchDraws = kSearchThreads / 16;
 
-    // The top level is the same for every draw: its prefix and total once.
-    uint64_t t0, t1, t2, t3, tc0, tc1, tc2, tc3;
-    load4_u64(lv.top, lv.top_size, lane * 4, t0, t1, t2, t3);
-    wave_prefix4(t0, t1, t2, t3, tc0, tc1, tc2, tc3);
-    const uint64_t S = read_lane(tc3, 63);
+template <bool kShard, int kTiles, bool kThree>
+__global__ __launch_bounds__(kSearchThreads) void search_kernel(const uint32_t* __restrict__ prio, int64_t N,
+                                                                Levels lv, int32_t B, uint64_t span, uint64_t seed,
+                                                                int want_min, Shard sh, uint32_t* __restrict__ wg_min,
+                                                                uint32_t* status, int64_t* __restrict__ idx,
+                                                                int32_t* __restrict__ start,
+                                                                uint32_t* __restrict__ sel_prio) {
+    __shared__ uint64_t top[kTopMax];  // inclusive prefix of the highest level
+    __shared__ uint64_t s_wave[kSearchThreads / 64];
+    __shared__ uint32_t s_min[kSearchThreads / 64];
+    // The arguments at once, not each where it is first used.
+    asm volatile("" ::"s"(prio), "s"(N), "s"(lv.top), "s"(lv.top_size), "s"(lv.level[0]), "s"(lv.size[0]), "s"(B),
+                 "s"(span), "s"(seed), "s"(idx), "s"(start), "s"(sel_prio));
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int sub = threadIdx.x & 15;  // lane within the draw's row
+    const int n = (int)lv.top_size;
+    {
+        uint64_t v0, v1, v2, v3;
+        load4_u64(lv.top, n, threadIdx.x * 4, v0, v1, v2, v3);
+        const uint64_t part = v0 + v1 + v2 + v3;
+        const uint64_t incl = wave_inclusive_scan(part);
+        if (lane == 63) s_wave[wave] = incl;
+        __syncthreads();
+        uint64_t c = incl - part;
+#pragma unroll
+        for (int k = 0; k < kSearchThreads / 64; k++) c += k < wave ? s_wave[k] : 0;
+        if ((int)threadIdx.x * 4 < n) {  // entries past n are never read
+            top[threadIdx.x * 4] = c += v0;
+            top[threadIdx.x * 4 + 1] = c += v1;
+            top[threadIdx.x * 4 + 2] = c += v2;
+            top[threadIdx.x * 4 + 3] = c += v3;
+        }
+        __syncthreads();
+    }
+    const uint64_t S = top[n - 1];
     // Draws are numbers in [0, S_all); this table owns [P, P + S).
     uint64_t S_all = S, P = 0;
     if (kShard) {
@@ -210,11 +252,14 @@ __global__ __launch_bounds__(256) void search_kernel(const uint32_t* __restrict_
         S_all = wave_sum(all);
         P = wave_sum(before);
     }
-    uint32_t my_min = 0xFFFFFFFFu;  // smallest priority this wave selected
+    uint32_t my_min = 0xFFFFFFFFu;  // smallest priority this row selected
 
-    for (int64_t b = wave_id; b < B; b += nwaves) {
+    // Every lane of a row takes the same branches, so row scans, counts and
+    // broadcasts see their whole row.
+    for (int64_t b = (int64_t)blockIdx.x * kSearchDraws + (threadIdx.x >> 4); b < B;
+         b += (int64_t)gridDim.x * kSearchDraws) {
         if (S_all == 0) {
-            if (lane == 0) {
+            if (sub == 0) {
                 idx[b] = -1;
                 start[b] = 0;
                 if (want_min) sel_prio[b] = 0u;
@@ -223,52 +268,162 @@ __global__ __launch_bounds__(256) void search_kernel(const uint32_t* __restrict_
             continue;
         }
         uint64_t r = scale_draw(splitmix64_out(seed, 2 * (uint64_t)b), S_all);
+        const int32_t st = (int32_t)scale_draw(splitmix64_out(seed, 2 * (uint64_t)b + 1), span);
         if (kShard) {
             if (r < P || r - P >= S) {  // another shard's draw: same window start, no slot
-                if (lane == 0) {
+                if (sub == 0) {
                     idx[b] = -1;
-                    start[b] = (int32_t)scale_draw(splitmix64_out(seed, 2 * (uint64_t)b + 1), span);
+                    start[b] = st;
                     if (want_min) sel_prio[b] = 0u;
                 }
                 continue;
             }
             r -= P;
         }
-        int64_t j = pick_child(tc0, tc1, tc2, tc3, r);
-        for (int l = top - 1; l >= 0; l--) {
-            uint64_t v0, v1, v2, v3, c0, c1, c2, c3;
-            load4_u64(lv.level[l], lv.size[l], j * kFanout + lane * 4, v0, v1, v2, v3);
-            wave_prefix4(v0, v1, v2, v3, c0, c1, c2, c3);
-            j = j * kFanout + pick_child(c0, c1, c2, c3, r);
+        // The node: the first prefix above r, which exists as r < S.
+        int j = 0;
+        if (n > 256) {
+            int e = sub * 64 + 63;
+            j = row_count(e < n && top[e] <= r) * 64;
+            e = j + sub * 4 + 3;
+            j += row_count(e < n && top[e] <= r) * 4;
+            e = j + sub;
+            j += row_count(sub < 4 && e < n && top[e] <= r);
+        } else {
+            int e = sub * 16 + 15;
+            j = row_count(e < n && top[e] <= r) * 16;
+            e = j + sub;
+            j += row_count(e < n && top[e] <= r);
         }
-        // j is the tile holding r: the same over its 256 priorities.
-        uint32_t p0, p1, p2, p3;
-        uint64_t c0, c1, c2, c3;
-        load4_u32(prio, N, j * kTile + lane * 4, p0, p1, p2, p3);
-        wave_prefix4(p0, p1, p2, p3, c0, c1, c2, c3);
-        const int cnt = pick_child(c0, c1, c2, c3, r);
-        if (lane == 0) {
-            idx[b] = (kShard ? sh.base : 0) + j * kTile + cnt;
-            start[b] = (int32_t)scale_draw(splitmix64_out(seed, 2 * (uint64_t)b + 1), span);
+        if (j > 0) r -= top[j - 1];
+        // Below, a row whose sums end at or before r (priorities changed under
+        // a running selection) takes the last lane: every index stays in range.
+        int64_t chunk = j;
+        if (kThree) {  // 256 chunks, 16 per lane
+            uint64_t v[16], sum = 0;
+#pragma unroll
+            for (int q = 0; q < 16; q += 4)
+                load4_u64(lv.level[1], lv.size[1], (int64_t)j * kFanout + sub * 16 + q, v[q], v[q + 1], v[q + 2],
+                          v[q + 3]);
+#pragma unroll
+            for (int q = 0; q < 16; q++) sum += v[q];
+            const uint64_t incl = row_inclusive_scan(sum);
+            uint64_t before = incl - sum, c = before;
+            int k = 0;
+#pragma unroll
+            for (int q = 0; q < 15; q++) {
+                c += v[q];
+                if (c <= r) {
+                    k = q + 1;
+                    before = c;
+                }
+            }
+            const int l = row_count(incl <= r);
+            const int from = l < 15 ? l : 15;
+            r -= __shfl(before, from, 16);
+            chunk = (int64_t)j * kFanout + from * 16 + __shfl(k, from, 16);
+            if (chunk >= lv.size[1]) chunk = lv.size[1] - 1;
         }
-        if (want_min) {
+        // The tile among the chunk's.
+        int64_t tile;
+        if (kTiles == 16) {
+            const int64_t e = chunk * kTiles + sub;
+            const uint64_t v = e < lv.size[0] ? lv.level[0][e] : 0;
+            const uint64_t incl = row_inclusive_scan(v);
+            const int l = row_count(incl <= r);
+            const int from = l < 15 ? l : 15;
+            r -= __shfl(incl - v, from, 16);
+            tile = chunk * kTiles + from;
+        } else {
+            uint64_t v0, v1, v2, v3, before;
+            load4_u64(lv.level[0], lv.size[0], chunk * kTiles + sub * 4, v0, v1, v2, v3);
+            const uint64_t sum = v0 + v1 + v2 + v3;
+            const uint64_t incl = row_inclusive_scan(sum);
+            const int k = pick_of4(v0, v1, v2, r - (incl - sum), before);
+            const int l = row_count(incl <= r);
+            const int from = l < 15 ? l : 15;
+            r -= __shfl(incl - sum + before, from, 16);
+            tile = chunk * kTiles + from * 4 + __shfl(k, from, 16);
+        }
+        if (tile >= lv.size[0]) tile = lv.size[0] - 1;
+        // The slot among the tile's 256 priorities.
+        uint32_t p[16];
+        const int64_t e0 = tile * kTile + sub * 16;
+        if ((tile + 1) * kTile <= N) {
+#pragma unroll
+            for (int q = 0; q < 16; q += 4) {
+                const uint4 v = *reinterpret_cast<const uint4*>(prio + e0 + q);
+                p[q] = v.x; p[q + 1] = v.y; p[q + 2] = v.z; p[q + 3] = v.w;
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < 16; q += 4) load4_u32(prio, N, e0 + q, p[q], p[q + 1], p[q + 2], p[q + 3]);
+        }
+        uint64_t s4[4];
+#pragma unroll
+        for (int q = 0; q < 4; q++) s4[q] = (uint64_t)p[4 * q] + p[4 * q + 1] + p[4 * q + 2] + p[4 * q + 3];
+        const uint64_t sum = s4[0] + s4[1] + s4[2] + s4[3];
+        const uint64_t incl = row_inclusive_scan(sum);
+        const int l = row_count(incl <= r);
+        const int from = l < 15 ? l : 15;
+        uint64_t rest = r - (incl - sum), before, unused;  // of use in lane `from` only
+        const int g = pick_of4(s4[0], s4[1], s4[2], rest, before);
+        rest -= before;
+        uint32_t a[4];
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+            a[q] = g == 0 ? p[q] : g == 1 ? p[4 + q] : g == 2 ? p[8 + q] : p[12 + q];
+        const int k = pick_of4(a[0], a[1], a[2], rest, unused);
+        const uint32_t mine = k == 0 ? a[0] : k == 1 ? a[1] : k == 2 ? a[2] : a[3];
+        const int at = __shfl(g * 4 + k, from, 16);
+        const uint32_t pv = __shfl(mine, from, 16);
+        if (sub == 0) {
+            int64_t slot = tile * kTile + from * 16 + at;
+            if (slot >= N) slot = N - 1;  // only under changing priorities
+            idx[b] = (kShard ? sh.base : 0) + slot;
+            start[b] = st;
             // The selected priority is kept for the weight kernel in the
             // caller's weight buffer, which that kernel then overwrites.
-            const uint32_t pv = (uint32_t)read_lane(pick4(p0, p1, p2, p3, cnt & 3), cnt >> 2);
-            my_min = pv < my_min ? pv : my_min;
-            if (lane == 0) sel_prio[b] = pv;
+            if (want_min) sel_prio[b] = pv;
         }
+        my_min = pv < my_min ? pv : my_min;
     }
     if (want_min) {
         // One slot per workgroup, no atomics: the weight kernel reduces them.
-        if (lane == 0) s_min[threadIdx.x >> 6] = my_min;
+        uint32_t o = __shfl_xor(my_min, 16);
+        my_min = o < my_min ? o : my_min;
+        o = __shfl_xor(my_min, 32);
+        my_min = o < my_min ? o : my_min;
+        if (lane == 0) s_min[wave] = my_min;
         __syncthreads();
         if (threadIdx.x == 0) {
             uint32_t m = s_min[0];
-            for (int k = 1; k < (int)(blockDim.x >> 6); k++) m = s_min[k] < m ? s_min[k] : m;
+            for (int k = 1; k < kSearchThreads / 64; k++) m = s_min[k] < m ? s_min[k] : m;
             wg_min[blockIdx.x] = m;
         }
     }
+}
+
+typedef void (*SearchKernel)(const uint32_t*, int64_t, Levels, int32_t, uint64_t, uint64_t, int, Shard, uint32_t*,
+                             uint32_t*, int64_t*, int32_t*, uint32_t*);
+
+SearchKernel search_variant(bool shard, int64_t N, int nlevels) {
+    if (tiles_per_chunk(N) == kSmallChunk)
+        return shard ? search_kernel<true, kSmallChunk, false> : search_kernel<false, kSmallChunk, false>;
+    if (nlevels == 2) return shard ? search_kernel<true, kLargeChunk, false> : search_kernel<false, kLargeChunk, false>;
+    return shard ? search_kernel<true, kLargeChunk, true> : search_kernel<false, kLargeChunk, true>;
+}
+
+int search_grid(int32_t B) {
+    const int64_t g = ((int64_t)B + kSearchDraws - 1) / kSearchDraws;  // one draw per row while the grid allows
+    return (int)(g < kSearchMaxGrid ? g : kSearchMaxGrid);
+}
+
+// (m / p)^beta for 0 < m, p: exp of beta * log, which is shorter than pow with
+// its special cases.  Both are off by a few units of 2^-53 times the exponent, far
+// below the rounding to fp32; equal priorities give 1 for every beta.
+__device__ __forceinline__ float is_weight(uint32_t m, uint32_t p, double beta) {
+    return m == p ? 1.0f : (float)exp(beta * log((double)m / (double)p));
 }
 
 // w_b = (n*P(i_b))^-beta / max_b' (n*P(i_b'))^-beta = (p_min / p_b)^beta,
@@ -280,10 +435,10 @@ __global__ __launch_bounds__(256) void is_weights_kernel(int32_t B, double beta,
                                                          int search_grid, float* __restrict__ w) {
     __shared__ uint32_t s_min[4];
     const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    // This draw's priority and the first eight minima per thread are loaded
+    // This draw's priority and the first four minima per thread are loaded
     // together, from indices clamped into their buffers, before any is used:
     // one memory round trip covers the search's largest grid.
-    constexpr int kMinPerThread = 8;
+    constexpr int kMinPerThread = kSearchMaxGrid / 256;
     const uint32_t pb_raw = reinterpret_cast<const uint32_t*>(w)[b < B ? b : B - 1];
     uint32_t v0[kMinPerThread];
 #pragma unroll
@@ -319,7 +474,7 @@ __global__ __launch_bounds__(256) void is_weights_kernel(int32_t B, double beta,
     m = s_min[0];
     for (int k = 1; k < (int)(blockDim.x >> 6); k++) m = s_min[k] < m ? s_min[k] : m;
     if (b >= B) return;
-    w[b] = (pb == 0u || m == 0u) ? 0.0f : (float)pow((double)m / (double)pb, beta);
+    w[b] = (pb == 0u || m == 0u) ? 0.0f : is_weight(m, pb, beta);
 }
 
 constexpr int kSmallThreads = 1024;
@@ -411,7 +566,7 @@ __global__ __launch_bounds__(kSmallThreads) void small_select_kernel(const uint3
     for (int q = 1; q < kSmallThreads / 64; q++) m = s_min[q] < m ? s_min[q] : m;
     for (int64_t b = t; b < B; b += kSmallThreads) {
         const uint32_t pb = reinterpret_cast<const uint32_t*>(w)[b];
-        w[b] = (pb == 0u || m == 0u) ? 0.0f : (float)pow((double)m / (double)pb, beta);
+        w[b] = (pb == 0u || m == 0u) ? 0.0f : is_weight(m, pb, beta);
     }
 }
 
@@ -429,40 +584,26 @@ __global__ void simple_select_kernel(SimpleDraws d, int32_t B, int64_t* __restri
     if (w) w[b] = 1.0f;
 }
 
-// The tree as the search sees it: level 0 and the copy of the upper levels
-// that the last scan filled.
+// The tree as the search sees it: of level 2, the copy the last scan filled.
 Levels tree(const Table& t) {
     Levels lv{};
     lv.nlevels = t.nlevels;
     for (int l = 0; l < t.nlevels; l++) {
-        lv.level[l] = l == 0 ? t.tile_sums : t.upper[t.tree_parity][l];
+        lv.level[l] = l == 0 ? t.tile_sums : l == 1 ? t.chunk_sums : t.upper[t.tree_parity];
         lv.size[l] = t.level_size[l];
     }
     return with_top(lv);
 }
 
-Levels upper_copy(const Table& t, int parity) {
-    Levels lv{};
-    lv.nlevels = t.nlevels;
-    for (int l = 1; l < t.nlevels; l++) {
-        lv.level[l] = t.upper[parity][l];
-        lv.size[l] = t.level_size[l];
-    }
-    return lv;
-}
-
 }  // namespace
 
 hipError_t launch_scan(Table& t, hipStream_t s) {
-    // The copy this scan fills was zeroed by the previous scan (or at
+    // The level-2 copy this scan fills was zeroed by the previous scan (or at
     // creation); this scan zeroes the other copy for the next one.
     const int par = 1 - t.tree_parity;
-    if (t.options & GEAR_OPT_IS_GLOBAL_MIN)
-        hipLaunchKernelGGL(scan_kernel<true>, dim3((unsigned)t.nchunks), dim3(256), 0, s, t.priority, t.N,
-                           upper_copy(t, par), upper_copy(t, 1 - par), t.tile_sums, t.ntiles, t.chunk_min);
-    else
-        hipLaunchKernelGGL(scan_kernel<false>, dim3((unsigned)t.nchunks), dim3(256), 0, s, t.priority, t.N,
-                           upper_copy(t, par), upper_copy(t, 1 - par), t.tile_sums, t.ntiles, t.chunk_min);
+    hipLaunchKernelGGL(scan_variant((t.options & GEAR_OPT_IS_GLOBAL_MIN) != 0, t.N), dim3((unsigned)t.nchunks),
+                       dim3(scan_threads(t.N)), 0, s, t.priority, t.N, t.upper[par], t.upper[1 - par], t.tile_sums,
+                       t.ntiles, t.chunk_sums, t.chunk_min);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) t.tree_parity = par;
     return e;
@@ -471,21 +612,15 @@ hipError_t launch_scan(Table& t, hipStream_t s) {
 hipError_t launch_search(Table& t, int32_t B, int32_t L, uint64_t seed, bool want_min, int64_t* idx,
                          int32_t* start, uint32_t* sel_prio, int* grid_out, hipStream_t s,
                          const uint64_t* shard_totals, int G, int g, int64_t base) {
-    int64_t gw = ((int64_t)B + 3) / 4;  // one wave per draw while the grid allows
-    const int grid = (int)(gw < kSearchMaxGrid ? gw : kSearchMaxGrid);
+    const int grid = search_grid(B);
     Shard sh;
     sh.totals = shard_totals;
     sh.G = G;
     sh.g = g;
     sh.base = base;
-    if (shard_totals)
-        hipLaunchKernelGGL(search_kernel<true>, dim3(grid), dim3(256), 0, s, t.priority, t.N, tree(t), B,
-                           (uint64_t)(t.T - L + 1), seed, want_min ? 1 : 0, sh, t.wg_min, t.status, idx, start,
-                           sel_prio);
-    else
-        hipLaunchKernelGGL(search_kernel<false>, dim3(grid), dim3(256), 0, s, t.priority, t.N, tree(t), B,
-                           (uint64_t)(t.T - L + 1), seed, want_min ? 1 : 0, sh, t.wg_min, t.status, idx, start,
-                           sel_prio);
+    const SearchKernel kernel = search_variant(shard_totals != nullptr, t.N, t.nlevels);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kSearchThreads), 0, s, t.priority, t.N, tree(t), B,
+                       (uint64_t)(t.T - L + 1), seed, want_min ? 1 : 0, sh, t.wg_min, t.status, idx, start, sel_prio);
     *grid_out = grid;
     return hipGetLastError();
 }
@@ -598,17 +733,14 @@ extern "C" int gear_select(gear_table* h, int32_t strategy, int32_t B, int32_t L
 namespace gear {
 namespace {
 
-constexpr int64_t kNaTiles = GEAR_NOALLOC_MAX_N / kTile;            // level 0 entries
-constexpr int64_t kNaLevel1 = (kNaTiles + kFanout - 1) / kFanout;     // level 1 entries (the top)
-static_assert(kNaLevel1 <= kFanout, "two levels cover every allowed table");
-static_assert(GEAR_NOALLOC_MAX_N % (kTile * kTilesPerChunk) == 0, "whole scan chunks");
-// Layout in 64-bit words: tile sums | level 1 (the scan adds into it) |
-// level 1 spare (the scan's zeroing target, never read) | wg_min (uint32) |
-// status (uint32).
+constexpr int64_t kNaTiles = GEAR_NOALLOC_MAX_N / kTile;   // level 0 entries
+constexpr int64_t kNaChunks = kTopMax;                       // level 1 entries (the highest level), at most
+static_assert(GEAR_NOALLOC_MAX_N <= (int64_t)kTopMax * kLargeChunk * kTile, "two levels cover every allowed table");
+// Layout in 64-bit words: tile sums | chunk sums | wg_min (uint32) | status
+// (uint32; set by the kernels, never read).  Every call rewrites what it reads.
 constexpr int64_t kNaOffTiles = 0;
-constexpr int64_t kNaOffLevel1 = kNaOffTiles + kNaTiles;
-constexpr int64_t kNaOffSpare = kNaOffLevel1 + kFanout;
-constexpr int64_t kNaOffMin = kNaOffSpare + kFanout;
+constexpr int64_t kNaOffChunks = kNaOffTiles + kNaTiles;
+constexpr int64_t kNaOffMin = kNaOffChunks + kNaChunks;
 constexpr int64_t kNaOffStatus = kNaOffMin + kSearchMaxGrid / 2;
 constexpr int64_t kNaWords = (kNaOffStatus + 1 + 31) / 32 * 32;
 static_assert(kNaWords * 8 == GEAR_NOALLOC_SCRATCH_BYTES, "header states the scratch size");
@@ -621,14 +753,6 @@ static __device__ __align__(256) uint64_t scratch[kNaWords];
 constexpr int kNaMaxDevices = 64;
 std::mutex g_na_mutex;
 uint64_t* g_na_ptr[kNaMaxDevices] = {};
-
-// Zeroes the level-1 nodes the scan accumulates into and the status word:
-// a kernel, not a memset, so that a captured graph replays it faithfully.
-__global__ void noalloc_clear_kernel(uint64_t* __restrict__ level1, uint32_t* __restrict__ status) {
-    const int k = threadIdx.x;
-    if (k < kFanout) level1[k] = 0;
-    if (k == 0) *status = 0u;
-}
 
 hipError_t noalloc_scratch(int dev, uint64_t** out) {
     std::lock_guard<std::mutex> lock(g_na_mutex);
@@ -677,33 +801,25 @@ extern "C" int gear_select_prioritized_noalloc(const uint32_t* d_priority, int64
         return e == hipSuccess ? GEAR_OK : hip_fail(e, "gear_select_prioritized_noalloc: small-table launch");
     }
     const int64_t ntiles = (N + kTile - 1) / kTile;
-    const int64_t nchunks = (ntiles + kTilesPerChunk - 1) / kTilesPerChunk;
-    Levels lv{}, upper{}, spare{};
-    lv.nlevels = ntiles > kFanout ? 2 : 1;
+    const int64_t nchunks = (ntiles + tiles_per_chunk(N) - 1) / tiles_per_chunk(N);
+    Levels lv{};
+    lv.nlevels = 2;
     lv.level[0] = base + kNaOffTiles;
     lv.size[0] = ntiles;
-    upper.nlevels = spare.nlevels = lv.nlevels;
-    if (lv.nlevels == 2) {
-        lv.level[1] = upper.level[1] = base + kNaOffLevel1;
-        spare.level[1] = base + kNaOffSpare;
-        lv.size[1] = upper.size[1] = spare.size[1] = (ntiles + kFanout - 1) / kFanout;
-    }
-    const char* what = "gear_select_prioritized_noalloc: clear launch";
-    hipLaunchKernelGGL(noalloc_clear_kernel, dim3(1), dim3(kFanout), 0, s, base + kNaOffLevel1, status);
-    if ((e = hipGetLastError()) == hipSuccess) {
-        what = "gear_select_prioritized_noalloc: scan launch";
-        hipLaunchKernelGGL(scan_kernel<false>, dim3((unsigned)nchunks), dim3(256), 0, s, d_priority, N, upper, spare,
-                           lv.level[0], ntiles, static_cast<uint32_t*>(nullptr));
-        e = hipGetLastError();
-    }
-    const int64_t gw = ((int64_t)B + 3) / 4;
-    const int grid = (int)(gw < kSearchMaxGrid ? gw : kSearchMaxGrid);
+    lv.level[1] = base + kNaOffChunks;
+    lv.size[1] = nchunks;
+    const char* what = "gear_select_prioritized_noalloc: scan launch";
+    hipLaunchKernelGGL(scan_variant(false, N), dim3((unsigned)nchunks), dim3(scan_threads(N)), 0, s, d_priority, N,
+                       static_cast<uint64_t*>(nullptr), static_cast<uint64_t*>(nullptr), lv.level[0], ntiles,
+                       lv.level[1], static_cast<uint32_t*>(nullptr));
+    e = hipGetLastError();
+    const int grid = search_grid(B);
     if (e == hipSuccess) {
         what = "gear_select_prioritized_noalloc: search launch";
         Shard sh{};
         sh.G = 1;
-        hipLaunchKernelGGL(search_kernel<false>, dim3(grid), dim3(256), 0, s, d_priority, N, with_top(lv), B, span,
-                           seed, d_weights ? 1 : 0, sh, wg_min, status, d_idx, d_start,
+        hipLaunchKernelGGL(search_variant(false, N, 2), dim3(grid), dim3(kSearchThreads), 0, s, d_priority, N,
+                           with_top(lv), B, span, seed, d_weights ? 1 : 0, sh, wg_min, status, d_idx, d_start,
                            reinterpret_cast<uint32_t*>(d_weights));
         e = hipGetLastError();
     }

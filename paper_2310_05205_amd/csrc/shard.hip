@@ -24,7 +24,7 @@ namespace {
 
 constexpr int kMaxShards = 4096;
 
-// Sum of the top level of the tree (at most 256 nodes), by one wave.
+// Sum of the top level of the tree (at most 1024 nodes), by one wave.
 __global__ void tree_total_kernel(const uint64_t* __restrict__ top, int64_t n, uint64_t* __restrict__ out) {
     uint64_t v = 0;
     for (int64_t k = threadIdx.x; k < n; k += 64) v += top[k];
@@ -304,7 +304,7 @@ extern "C" int gear_shard_total(gear_table* h, uint64_t* d_total, void* stream) 
         t->cdf_dirty = false;
     }
     const int top = t->nlevels - 1;
-    const uint64_t* lv = top == 0 ? t->tile_sums : t->upper[t->tree_parity][top];
+    const uint64_t* lv = top == 1 ? t->chunk_sums : t->upper[t->tree_parity];
     hipLaunchKernelGGL(gear::tree_total_kernel, dim3(1), dim3(64), 0, s, lv, t->level_size[top], d_total);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "gear_shard_total: launch");
     return GEAR_OK;

@@ -74,8 +74,8 @@ void free_table(Table* t) {
     (void)hipFree(t->priority);
     (void)hipFree(t->tag);
     (void)hipFree(t->tile_sums);
-    for (int c = 0; c < 2; c++)
-        for (int l = 0; l < gear::kMaxLevels; l++) (void)hipFree(t->upper[c][l]);
+    (void)hipFree(t->chunk_sums);
+    for (int c = 0; c < 2; c++) (void)hipFree(t->upper[c]);
     (void)hipFree(t->wg_min);
     (void)hipFree(t->chunk_min);
     (void)hipFree(t->topk_hist);
@@ -252,27 +252,23 @@ int create_table(const int64_t* elem_bytes, int32_t ncols, int64_t capacity, int
 
     // Sum tree geometry.
     t->ntiles = (capacity + gear::kTile - 1) / gear::kTile;
-    t->nchunks = (t->ntiles + gear::kTilesPerChunk - 1) / gear::kTilesPerChunk;
-    int64_t sz = t->ntiles;
-    t->nlevels = 0;
-    while (true) {
-        t->level_size[t->nlevels] = sz;
-        t->nlevels++;
-        if (sz <= gear::kFanout) break;
-        sz = (sz + gear::kFanout - 1) / gear::kFanout;
-    }
+    t->nchunks = (t->ntiles + gear::tiles_per_chunk(capacity) - 1) / gear::tiles_per_chunk(capacity);
+    t->level_size[0] = t->ntiles;
+    t->level_size[1] = t->nchunks;
+    t->level_size[2] = (t->nchunks + gear::kFanout - 1) / gear::kFanout;
+    t->nlevels = t->nchunks > gear::kTopMax ? 3 : 2;
     if ((e = dmalloc(hook, &t->priority, sizeof(uint32_t) * capacity)) != hipSuccess) return oom("priorities", e);
     if ((e = dmalloc(hook, &t->tag, sizeof(uint32_t) * capacity)) != hipSuccess) return oom("scatter tags", e);
     if ((e = dmalloc(hook, &t->tile_sums, sizeof(uint64_t) * t->ntiles)) != hipSuccess) return oom("tile sums", e);
-    for (int c = 0; c < 2; c++)
-        for (int l = 1; l < t->nlevels; l++) {
-            if ((e = dmalloc(hook, &t->upper[c][l], sizeof(uint64_t) * t->level_size[l])) != hipSuccess)
-                return oom("sum tree levels", e);
-            if ((e = hipMemset(t->upper[c][l], 0, sizeof(uint64_t) * t->level_size[l])) != hipSuccess) {
-                free_table(t);
-                return hip_fail(e, "gear_table_create: clearing the sum tree");
-            }
+    if ((e = dmalloc(hook, &t->chunk_sums, sizeof(uint64_t) * t->nchunks)) != hipSuccess) return oom("chunk sums", e);
+    for (int c = 0; c < 2 && t->nlevels == 3; c++) {
+        if ((e = dmalloc(hook, &t->upper[c], sizeof(uint64_t) * t->level_size[2])) != hipSuccess)
+            return oom("sum tree levels", e);
+        if ((e = hipMemset(t->upper[c], 0, sizeof(uint64_t) * t->level_size[2])) != hipSuccess) {
+            free_table(t);
+            return hip_fail(e, "gear_table_create: clearing the sum tree");
         }
+    }
     if ((e = dmalloc(hook, &t->wg_min, sizeof(uint32_t) * gear::kSearchMaxGrid)) != hipSuccess) return oom("batch minima", e);
     if ((e = dmalloc(hook, &t->chunk_min, sizeof(uint32_t) * t->nchunks)) != hipSuccess) return oom("chunk minima", e);
     if ((e = dmalloc(hook, &t->status, sizeof(uint32_t))) != hipSuccess) return oom("status word", e);
@@ -300,6 +296,7 @@ int create_table(const int64_t* elem_bytes, int32_t ncols, int64_t capacity, int
     if ((e = hipMemset(t->priority, 0, sizeof(uint32_t) * capacity)) != hipSuccess ||
         (e = hipMemset(t->tag, 0, sizeof(uint32_t) * capacity)) != hipSuccess ||
         (e = hipMemset(t->tile_sums, 0, sizeof(uint64_t) * t->ntiles)) != hipSuccess ||
+        (e = hipMemset(t->chunk_sums, 0, sizeof(uint64_t) * t->nchunks)) != hipSuccess ||
         (e = hipMemset(t->wg_min, 0xFF, sizeof(uint32_t) * gear::kSearchMaxGrid)) != hipSuccess ||
         (e = hipMemset(t->status, 0, sizeof(uint32_t))) != hipSuccess ||
         (e = hipMemset(t->topk_hist, 0, sizeof(uint32_t) * 3 * gear::kTopkBins)) != hipSuccess ||

@@ -45,18 +45,30 @@ constexpr int kAggNodes = 1024;                     // ... when they have at mos
 
 struct Tree {
     uint64_t* tile_sums;             // level 0
-    uint64_t* upper[kMaxLevels];     // levels 1 .. nlevels-1 (the copy the last scan filled)
+    uint64_t* upper[kMaxLevels];     // levels 1 .. nlevels-1 (of level 2, the copy the last scan filled)
     int64_t size[kMaxLevels];
     int nlevels;
+    int chunk_shift;                 // a level-1 node covers 2^chunk_shift slots, a level-2 node 2^22
     int maintain;                    // 0: leave the tree alone
 };
-
-// Level l >= 1 node covering `slot`: a level-l node covers 256^l tiles of 256.
-__device__ inline int64_t node_of(int64_t slot, int l) { return slot >> (8 * (l + 1)); }
 
 __device__ inline void add_u64(uint64_t* p, uint64_t d) {
     atomicAdd(reinterpret_cast<unsigned long long*>(p), (unsigned long long)d);
 }
+
+// Adds d into the level-1 and level-2 nodes covering `slot`.  Written out per
+// level: from a loop over the levels the compiler formed one induction variable
+// for the shift and for the address of tree.upper[l], and read the pointer with
+// a scalar load of base + 14 and offset 0x32, whose two lowest address bits the
+// hardware drops from each part.
+constexpr int kLevel2Shift = 22;
+static_assert(kTile * kLargeChunk * kFanout == 1 << kLevel2Shift, "slots per level-2 node");
+__device__ __forceinline__ void add_upper(const Tree& tree, int64_t slot, uint64_t d) {
+    add_u64(tree.upper[1] + (slot >> tree.chunk_shift), d);
+    if (tree.nlevels == 3) add_u64(tree.upper[2] + (slot >> kLevel2Shift), d);
+}
+static_assert(kMaxLevels == 3, "levels 1 and 2 are written out");
+static_assert(GEAR_MAX_CAPACITY >> 22 <= kAggNodes, "level 2 fits the LDS counters");
 
 // `live`: indices at or past it are invalid.  `committed` (managed tables
 // only, else NULL): an index whose flag is 0 is released or still being
@@ -69,6 +81,7 @@ __global__ __launch_bounds__(kHashThreads) void scatter_lds_kernel(const int64_t
     __shared__ uint32_t key[kHashSize];
     __shared__ uint32_t tag[kHashSize];
     __shared__ uint64_t agg[kAggLevels][kAggNodes];
+    const bool agg1 = tree.size[1] <= kAggNodes;  // level 2 always fits: at most 256 nodes
     for (int h = threadIdx.x; h < kHashSize; h += kHashThreads) {
         key[h] = kEmpty;
         tag[h] = 0u;
@@ -145,22 +158,20 @@ __global__ __launch_bounds__(kHashThreads) void scatter_lds_kernel(const int64_t
         const uint64_t d = (uint64_t)val[k] - (uint64_t)old[k];  // mod 2^64
         if (d == 0) continue;
         add_u64(tree.tile_sums + (s >> 8), d);
-        for (int l = 1; l < tree.nlevels; l++) {
-            const int64_t n = node_of(s, l);
-            if (l <= kAggLevels && tree.size[l] <= kAggNodes)
-                atomicAdd(reinterpret_cast<unsigned long long*>(&agg[l - 1][n]), (unsigned long long)d);
-            else
-                add_u64(tree.upper[l] + n, d);
-        }
+        if (agg1) atomicAdd(reinterpret_cast<unsigned long long*>(&agg[0][s >> tree.chunk_shift]), (unsigned long long)d);
+        else add_u64(tree.upper[1] + (s >> tree.chunk_shift), d);
+        if (tree.nlevels == 3)
+            atomicAdd(reinterpret_cast<unsigned long long*>(&agg[1][s >> kLevel2Shift]), (unsigned long long)d);
     }
     if (bad) atomicOr(status, GEAR_STATUS_BAD_INDEX);
     if (!tree.maintain) return;
     __syncthreads();
-    for (int l = 1; l < tree.nlevels && l <= kAggLevels; l++) {
-        if (tree.size[l] > kAggNodes) continue;
-        for (int n = threadIdx.x; n < tree.size[l]; n += kHashThreads)
-            if (agg[l - 1][n] != 0) add_u64(tree.upper[l] + n, agg[l - 1][n]);
-    }
+    if (agg1)
+        for (int n = threadIdx.x; n < tree.size[1]; n += kHashThreads)
+            if (agg[0][n] != 0) add_u64(tree.upper[1] + n, agg[0][n]);
+    if (tree.nlevels == 3)
+        for (int n = threadIdx.x; n < tree.size[2]; n += kHashThreads)
+            if (agg[1][n] != 0) add_u64(tree.upper[2] + n, agg[1][n]);
 }
 
 __global__ void scatter_tag_kernel(const int64_t* __restrict__ idx, int32_t B, int64_t live,
@@ -191,7 +202,7 @@ __global__ void scatter_apply_kernel(const int64_t* __restrict__ idx, const uint
             const uint64_t d = (uint64_t)newp[b] - (uint64_t)old;  // mod 2^64
             if (d != 0) {
                 add_u64(tree.tile_sums + (i >> 8), d);
-                for (int l = 1; l < tree.nlevels; l++) add_u64(tree.upper[l] + node_of(i, l), d);
+                add_upper(tree, i, d);
             }
         }
     }
@@ -202,9 +213,11 @@ Tree tree_of(const Table& t, bool maintain) {
     tr.tile_sums = t.tile_sums;
     tr.nlevels = t.nlevels;
     for (int l = 0; l < t.nlevels; l++) {
-        tr.upper[l] = l == 0 ? nullptr : t.upper[t.tree_parity][l];
+        tr.upper[l] = l == 0 ? nullptr : l == 1 ? t.chunk_sums : t.upper[t.tree_parity];
         tr.size[l] = t.level_size[l];
     }
+    tr.chunk_shift = tiles_per_chunk(t.N) == kSmallChunk ? 12 : 14;
+    static_assert(kTile * kSmallChunk == 1 << 12 && kTile * kLargeChunk == 1 << 14, "slots per chunk");
     tr.maintain = maintain ? 1 : 0;
     return tr;
 }

@@ -106,8 +106,4 @@ __device__ __forceinline__ uint64_t read_lane(uint64_t v, int src) {
 
 __device__ __forceinline__ uint64_t wave_sum(uint64_t v) { return read_lane(wave_inclusive_scan(v), 63); }
 
-__device__ __forceinline__ uint64_t pick4(uint64_t a, uint64_t b, uint64_t c, uint64_t d, int q) {
-    return q == 0 ? a : (q == 1 ? b : (q == 2 ? c : d));
-}
-
 }  // namespace gear
