@@ -4,13 +4,13 @@
 // The batch is applied as if in order, so for a slot that appears several
 // times the last occurrence's value wins.
 //
-// Batches of up to 8192 run in one launch of 32 workgroups.  Workgroup g
-// owns the slots whose hash falls in partition g: it reads the whole batch,
-// inserts each of its draws' slots into an open-addressing hash table in LDS
-// and raises that entry's tag to b+1 (LDS atomic max); after a barrier the
-// draw whose b+1 equals its entry's tag is the last occurrence of its slot
-// and writes the new priority.  Every occurrence of a slot lands in the
-// same workgroup, so no other synchronisation is needed.
+// Batches of up to 8192 run in one launch of 64 workgroups.  Workgroup g owns
+// the slots whose hash falls in partition g: it reads the whole batch, lists
+// its draws, and enters each into an open-addressing hash table in LDS, whose
+// entry for a slot holds b+1 of the last draw that has it (LDS atomic max);
+// after a barrier the draw that its slot's entry names writes the new priority.
+// Every occurrence of a slot lands in the same workgroup, so no other
+// synchronisation is needed.
 //
 // Larger batches use two kernels over a table-owned tag array:
 //   tag    every draw b raises tag[slot] to b+1 (atomic max), so after the
@@ -33,15 +33,9 @@ namespace gear {
 namespace {
 
 constexpr int kHashThreads = 1024;
-constexpr int kHashMaxBatch = 8192;                 // load factor <= 1/2
-constexpr int kHashBits = 14;
-constexpr int kHashSize = 1 << kHashBits;           // 2 x 64 KiB of LDS
-constexpr int kPerThread = kHashMaxBatch / kHashThreads;
-constexpr uint32_t kEmpty = 0xFFFFFFFFu;            // never a slot: slots are < 2^30
-constexpr int kPartBits = 5;
-constexpr int kParts = 1 << kPartBits;              // workgroups of the one-launch path
-constexpr int kAggLevels = 2;                       // upper levels combined in LDS
-constexpr int kAggNodes = 1024;                     // ... when they have at most this many nodes
+constexpr int kHashMaxBatch = 8 * kHashThreads;     // draws of the one-launch path
+constexpr int kAggNodes = 1024;                     // level-1 nodes combined in LDS, when there are no more
+constexpr int kLevel2Max = GEAR_MAX_CAPACITY >> 22; // level-2 nodes, always combined in LDS
 
 struct Tree {
     uint64_t* tile_sums;             // level 0
@@ -68,110 +62,119 @@ __device__ __forceinline__ void add_upper(const Tree& tree, int64_t slot, uint64
     if (tree.nlevels == 3) add_u64(tree.upper[2] + (slot >> kLevel2Shift), d);
 }
 static_assert(kMaxLevels == 3, "levels 1 and 2 are written out");
-static_assert(GEAR_MAX_CAPACITY >> 22 <= kAggNodes, "level 2 fits the LDS counters");
+static_assert(kLevel2Max <= kHashThreads, "one thread per level-2 node");
 
 // `live`: indices at or past it are invalid.  `committed` (managed tables
 // only, else NULL): an index whose flag is 0 is released or still being
 // written; its update is dropped, so it never becomes selectable.
+//
+// kHashThreads * kPerThread draws at most, in 2^part_bits workgroups.  With one
+// draw per thread a thread keeps its own; with more, the draws of the partition
+// are listed first, so that the code behind exists once and not per draw: an
+// earlier kernel that unrolled all of it over eight draws was bound by fetching
+// its instructions and took the same 4.5 us for 1 draw as for 1000.  Replayed
+// from a graph, before -> after: 256 draws 4.5 -> 2.4 us, 1000 4.6 -> 2.7, 3001
+// 5.0 -> 3.6, 8192 6.4 -> 4.9; keeping the tree, 256 5.3 -> 3.0, 8192 8.3 -> 6.0.
+template <int kPerThread>
 __global__ __launch_bounds__(kHashThreads) void scatter_lds_kernel(const int64_t* __restrict__ idx,
                                                                    const uint32_t* __restrict__ newp, int32_t B,
                                                                    int64_t live, const uint8_t* __restrict__ committed,
-                                                                   uint32_t* __restrict__ prio,
-                                                                   uint32_t* status, Tree tree) {
-    __shared__ uint32_t key[kHashSize];
-    __shared__ uint32_t tag[kHashSize];
-    __shared__ uint64_t agg[kAggLevels][kAggNodes];
-    const bool agg1 = tree.size[1] <= kAggNodes;  // level 2 always fits: at most 256 nodes
-    for (int h = threadIdx.x; h < kHashSize; h += kHashThreads) {
-        key[h] = kEmpty;
-        tag[h] = 0u;
-    }
-    for (int h = threadIdx.x; h < kAggLevels * kAggNodes; h += kHashThreads) agg[h / kAggNodes][h % kAggNodes] = 0;
+                                                                   uint32_t* __restrict__ prio, uint32_t* status,
+                                                                   int part_bits, Tree tree) {
+    constexpr int kThreads = kHashThreads;
+    constexpr int kMost = kThreads * kPerThread;  // a partition may hold every draw
+    constexpr int kSize = 2 * kMost;              // hash entries: load factor <= 1/2
+    constexpr int kBits = __builtin_ctz(kSize);
+    constexpr bool kList = kPerThread > 1;
+    __shared__ __align__(16) uint32_t last[kSize];    // b + 1 of the last draw seen of the entry's slot, 0 if free
+    __shared__ uint32_t own_slot[kMost];              // slot of draw b, for draws of this partition
+    __shared__ uint16_t own_b[kList ? kMost : 1];     // those draws, in any order
+    __shared__ int n_own;
+    __shared__ uint64_t agg1[kAggNodes];              // additions to level 1 and level 2
+    __shared__ uint64_t agg2[kLevel2Max];
+    const bool in_lds = tree.size[1] <= kAggNodes;
+    // The batch's loads first, from indices clamped into it: the tables are
+    // cleared while they are on their way.
     int64_t slot[kPerThread];
-    uint32_t val[kPerThread];
 #pragma unroll
     for (int k = 0; k < kPerThread; k++) {
-        const int b = threadIdx.x + k * kHashThreads;
-        slot[k] = b < B ? idx[b] : -1;
-        val[k] = b < B ? newp[b] : 0u;
+        const int b = threadIdx.x + k * kThreads;
+        slot[k] = idx[b < B ? b : B - 1];
     }
-    // Draws of this workgroup's partition.  Their committed flags and old
-    // priorities are read now, overlapping the hash phase, all issued
-    // before any is used.  Draws of other partitions and invalid ones read
-    // slot 0 instead, the same word for every such lane, and ignore it:
-    // each workgroup then fetches only its own ~B/32 scattered words, not
-    // all B (reading every draw's old priority in all 32 workgroups made an
-    // update that keeps the tree 15.7 instead of 9.7 us).  Only the winning
-    // draw of a slot writes it, and only after the barrier below.
-    bool mine[kPerThread];
-    bool part[kPerThread];
-    uint32_t old[kPerThread];
-    uint32_t flag[kPerThread];
+    if (kList && threadIdx.x == 0) n_own = 0;
+    for (int h = threadIdx.x * 4; h < kSize; h += kThreads * 4)
+        *reinterpret_cast<uint4*>(&last[h]) = make_uint4(0u, 0u, 0u, 0u);
+    if (tree.maintain) {
+        for (int m = threadIdx.x; m < kAggNodes; m += kThreads) agg1[m] = 0;
+        if (threadIdx.x < kLevel2Max) agg2[threadIdx.x] = 0;
+    }
+    if (kList) __syncthreads();
     bool bad = false;
+    int n = 0;  // own draws of the workgroup; without a list, 1 for a thread that has one
 #pragma unroll
     for (int k = 0; k < kPerThread; k++) {
-        const int b = threadIdx.x + k * kHashThreads;
-        const bool valid = b < B && slot[k] >= 0 && slot[k] < live;
-        part[k] = valid && (((uint32_t)slot[k] * 0x85EBCA6Bu) >> (32 - kPartBits)) == blockIdx.x;
-        const int64_t s = part[k] ? slot[k] : 0;
-        flag[k] = committed != nullptr ? committed[s] : 1u;
-        old[k] = tree.maintain ? prio[s] : 0u;
-    }
-    static_assert(kPerThread == 8, "the values below are listed per draw");
-    // Keeps the compiler from waiting on each load before issuing the next.
-    asm volatile("" ::"v"(flag[0]), "v"(flag[1]), "v"(flag[2]), "v"(flag[3]), "v"(flag[4]), "v"(flag[5]),
-                 "v"(flag[6]), "v"(flag[7]), "v"(old[0]), "v"(old[1]), "v"(old[2]), "v"(old[3]), "v"(old[4]),
-                 "v"(old[5]), "v"(old[6]), "v"(old[7]));
-#pragma unroll
-    for (int k = 0; k < kPerThread; k++) {
-        const int b = threadIdx.x + k * kHashThreads;
-        const bool valid = b < B && slot[k] >= 0 && slot[k] < live;
-        if (b < B && !valid && blockIdx.x == 0) bad = true;
-        mine[k] = part[k] && flag[k] != 0;
-        if (!mine[k]) old[k] = 0u;
-    }
-    __syncthreads();
-    int pos[kPerThread];
-#pragma unroll
-    for (int k = 0; k < kPerThread; k++) {
-        const int b = threadIdx.x + k * kHashThreads;
-        pos[k] = -1;
-        if (!mine[k]) continue;
-        const uint32_t kk = (uint32_t)slot[k];
-        uint32_t h = (kk * 2654435761u) >> (32 - kHashBits);
-        while (true) {  // at most B < kHashSize occupied entries, so a free or equal key is found
-            const uint32_t prev = atomicCAS(&key[h], kEmpty, kk);
-            if (prev == kEmpty || prev == kk) break;
-            h = (h + 1) & (kHashSize - 1);
+        const int b = threadIdx.x + k * kThreads;
+        const bool valid = slot[k] >= 0 && slot[k] < live;
+        bad = bad || !valid;  // a clamped index repeats the batch's last draw
+        if (b < B && valid && ((uint32_t)slot[k] * 0x85EBCA6Bu) >> (32 - part_bits) == blockIdx.x) {
+            own_slot[b] = (uint32_t)slot[k];
+            if (kList) own_b[atomicAdd(&n_own, 1)] = (uint16_t)b;
+            else n = (int)threadIdx.x + 1;
         }
-        atomicMax(&tag[h], (uint32_t)(b + 1));
-        pos[k] = (int)h;
     }
     __syncthreads();
-#pragma unroll
-    for (int k = 0; k < kPerThread; k++) {
-        const int b = threadIdx.x + k * kHashThreads;
-        if (pos[k] < 0 || tag[pos[k]] != (uint32_t)(b + 1)) continue;
-        const int64_t s = slot[k];
-        prio[s] = val[k];
+    if (kList) n = n_own;
+    // Value and old priority of this thread's first own draw (usually the
+    // only one), issued before the hash phase and used after it.
+    const int i0 = threadIdx.x;
+    uint32_t val0 = 0, old0 = 0;
+    if (i0 < n) {
+        const int b = kList ? own_b[i0] : i0;
+        val0 = newp[b];
+        old0 = tree.maintain ? prio[own_slot[b]] : 0u;
+    }
+    for (int i = i0; i < n; i += kThreads) {
+        const int b = kList ? own_b[i] : i;
+        const uint32_t s = own_slot[b];
+        if (committed != nullptr && committed[s] == 0) continue;
+        uint32_t h = (s * 2654435761u) >> (32 - kBits);
+        while (true) {  // at most kMost < kSize distinct slots, so a free or equal entry is found
+            const uint32_t was = atomicCAS(&last[h], 0u, (uint32_t)b + 1);
+            if (was == 0) break;
+            if (own_slot[was - 1] == s) {  // an entry's slot never changes
+                atomicMax(&last[h], (uint32_t)b + 1);
+                break;
+            }
+            h = (h + 1) & (kSize - 1);
+        }
+    }
+    __syncthreads();
+    for (int i = i0; i < n; i += kThreads) {
+        const int b = kList ? own_b[i] : i;
+        const uint32_t s = own_slot[b];
+        uint32_t h = (s * 2654435761u) >> (32 - kBits);
+        uint32_t e;
+        while ((e = last[h]) != 0 && own_slot[e - 1] != s) h = (h + 1) & (kSize - 1);
+        if (e != (uint32_t)b + 1) continue;  // a later draw of the slot wins, or the update is dropped
+        const uint32_t val = i == i0 ? val0 : newp[b];
+        const uint32_t old = i == i0 ? old0 : tree.maintain ? prio[s] : 0u;
+        prio[s] = val;
         if (!tree.maintain) continue;
-        const uint64_t d = (uint64_t)val[k] - (uint64_t)old[k];  // mod 2^64
+        const uint64_t d = (uint64_t)val - (uint64_t)old;  // mod 2^64
         if (d == 0) continue;
         add_u64(tree.tile_sums + (s >> 8), d);
-        if (agg1) atomicAdd(reinterpret_cast<unsigned long long*>(&agg[0][s >> tree.chunk_shift]), (unsigned long long)d);
+        if (in_lds) add_u64(&agg1[s >> tree.chunk_shift], d);
         else add_u64(tree.upper[1] + (s >> tree.chunk_shift), d);
-        if (tree.nlevels == 3)
-            atomicAdd(reinterpret_cast<unsigned long long*>(&agg[1][s >> kLevel2Shift]), (unsigned long long)d);
+        if (tree.nlevels == 3) add_u64(&agg2[s >> kLevel2Shift], d);
     }
-    if (bad) atomicOr(status, GEAR_STATUS_BAD_INDEX);
+    if (bad && blockIdx.x == 0) atomicOr(status, GEAR_STATUS_BAD_INDEX);
     if (!tree.maintain) return;
     __syncthreads();
-    if (agg1)
-        for (int n = threadIdx.x; n < tree.size[1]; n += kHashThreads)
-            if (agg[0][n] != 0) add_u64(tree.upper[1] + n, agg[0][n]);
-    if (tree.nlevels == 3)
-        for (int n = threadIdx.x; n < tree.size[2]; n += kHashThreads)
-            if (agg[1][n] != 0) add_u64(tree.upper[2] + n, agg[1][n]);
+    if (in_lds)
+        for (int m = threadIdx.x; m < tree.size[1]; m += kThreads)
+            if (agg1[m] != 0) add_u64(tree.upper[1] + m, agg1[m]);
+    if (tree.nlevels == 3 && threadIdx.x < tree.size[2] && agg2[threadIdx.x] != 0)
+        add_u64(tree.upper[2] + threadIdx.x, agg2[threadIdx.x]);
 }
 
 __global__ void scatter_tag_kernel(const int64_t* __restrict__ idx, int32_t B, int64_t live,
@@ -232,8 +235,16 @@ hipError_t launch_scatter(Table& t, const int64_t* idx, const uint32_t* newp, in
     const uint8_t* committed = t.managed ? t.committed : nullptr;
     const Tree tree = tree_of(t, maintain_tree);
     if (B <= kHashMaxBatch) {
-        hipLaunchKernelGGL(scatter_lds_kernel, dim3(kParts), dim3(kHashThreads), 0, s, idx, newp, B, live,
-                           committed, t.priority, t.status, tree);
+        // 64 workgroups, or 32 where each also adds its nodes' sums into the
+        // tree (8192 draws: 64 / 32 workgroups 4.9 / 5.0 us without the tree,
+        // 6.3 / 6.0 with it; 128 gain 0.1 us and hold twice as many CUs' LDS).
+        const int bits = maintain_tree ? 5 : 6;
+        const auto kernel = B <= kHashThreads       ? scatter_lds_kernel<1>
+                            : B <= 2 * kHashThreads ? scatter_lds_kernel<2>
+                            : B <= 4 * kHashThreads ? scatter_lds_kernel<4>
+                                                    : scatter_lds_kernel<8>;
+        hipLaunchKernelGGL(kernel, dim3(1u << bits), dim3(kHashThreads), 0, s, idx, newp, B, live, committed,
+                           t.priority, t.status, bits, tree);
         return hipGetLastError();
     }
     const unsigned grid = (unsigned)((B + 255) / 256);
