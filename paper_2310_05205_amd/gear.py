@@ -6,7 +6,9 @@ and only marshals arguments: pointers are Python ints (a torch tensor's
 ``cuda_stream``; 0 is the null stream).  Every step of the hot path runs in
 the HIP library; a failing call raises ``GearError``.  ``Table`` is a
 convenience wrapper that takes torch tensors and uses torch only to allocate
-device memory and to name the current stream.
+device memory and to name the current stream.  Its calls of every step go
+through the native module ``_binding`` (built beside libgear.so), which
+allocates the outputs and makes the C call in one go.
 """
 import ctypes
 import os
@@ -66,6 +68,32 @@ class GearError(RuntimeError):
 
 
 _lib = None
+_native = None
+
+
+def native():
+    """The native module of the per-step calls, bound to lib()."""
+    global _native
+    if _native is None:
+        import torch  # noqa: F401  (the module's symbols come from torch's libraries)
+        try:
+            from . import _binding
+        except ImportError as e:
+            raise RuntimeError("_binding.so is not built or does not load (%s): run __graft_entry__.build() "
+                               "or python -m paper_2310_05205_amd.build" % e)
+        L = lib()
+        _binding.bind(*[ctypes.cast(f, ctypes.c_void_p).value for f in
+                        (L.gear_select, L.gear_collect, L.gear_select_collect, L.gear_update_priorities,
+                         L.gear_select_shard, L.gear_is_weights, L.gear_topk_merge)])
+        _native = _binding
+    return _native
+
+
+def _result(r):
+    """A native call's results; its status as an exception when it is an int."""
+    if type(r) is int:
+        _check(r)
+    return r
 
 
 def lib():
@@ -297,17 +325,8 @@ def topk_merge(prio, gidx, K, T, L, seed, device=0):
     uint32-valued priorities and int64 global indices on `device`).
     Returns (idx, start, weights, priorities)."""
     import torch
-    dev = torch.device("cuda", device)
-    G = int(gidx.shape[0])
-    idx = torch.empty(K, dtype=torch.int64, device=dev)
-    start = torch.empty(K, dtype=torch.int32, device=dev)
-    w = torch.empty(K, dtype=torch.float32, device=dev)
-    p = torch.empty(K, dtype=torch.int32, device=dev)
-    prio = prio.contiguous()
-    gidx = gidx.contiguous()
-    gear_topk_merge(prio.data_ptr(), gidx.data_ptr(), G, K, T, L, seed, idx.data_ptr(), start.data_ptr(),
-                    w.data_ptr(), p.data_ptr(), torch.cuda.current_stream(dev).cuda_stream)
-    return idx, start, w, p
+    return _result(native().topk_merge(prio.contiguous(), gidx.contiguous(), int(gidx.shape[0]), K, int(T), int(L),
+                                       int(seed), device, torch._C._cuda_getCurrentRawStream(device)))
 
 
 class _DeviceBytes:
@@ -385,6 +404,10 @@ class Table:
             name, dtype, elems = gear_table_column_info(self.handle, c)
             self.columns.append(ColumnSpec(name, dtype, specs[c].shape if typed else (elems,)))
         self._index = {c.name: i for i, c in enumerate(self.columns)}
+        self._names = [c.name for c in self.columns]
+        self._native = native()
+        self._plan = self._native.plan([(c.torch_dtype(), c.shape, eb)
+                                        for c, eb in zip(self.columns, self.elem_bytes)])
 
     def close(self):
         if self.handle:
@@ -400,7 +423,7 @@ class Table:
     def _stream(self, stream):
         if stream is not None:
             return stream.cuda_stream
-        return self._torch.cuda.current_stream(self.device).cuda_stream
+        return self._torch._C._cuda_getCurrentRawStream(self.device)
 
     def _sources(self, col_src):
         """Pointers of the column sources, in column order: a list, or a dict
@@ -423,65 +446,54 @@ class Table:
         gear_insert(self.handle, n, self._sources(col_src), _data_ptr(priorities), self._stream(stream))
 
     def select(self, strategy, B, L, seed, beta=0.0, weights=False, stream=None):
-        torch = self._torch
-        dev = torch.device("cuda", self.device)
-        idx = torch.empty(B, dtype=torch.int64, device=dev)
-        start = torch.empty(B, dtype=torch.int32, device=dev)
-        w = torch.empty(B, dtype=torch.float32, device=dev) if weights else None
-        gear_select(self.handle, strategy, B, L, seed, beta, idx.data_ptr(), start.data_ptr(),
-                    w.data_ptr() if w is not None else 0, self._stream(stream))
-        return idx, start, w
+        return _result(self._native.select(self.handle, int(strategy), B, int(L), int(seed), beta, weights,
+                                           self.device, self._stream(stream)))
+
+    def _collect(self, idx, start, L, col_ids, typed, stream):
+        """Newly allocated batches of columns `col_ids` (None: all), typed
+        [B, L, *shape] or bytes [B, L*E_c]."""
+        return _result(self._native.collect(self.handle, self._plan, idx, start, L, col_ids, typed, self.device,
+                                            self._stream(stream)))
 
     def collect(self, idx, start, L, col_ids=None, stream=None, out=None):
         """Returns a list of uint8 tensors [B, L*E_c], one per requested column."""
-        torch = self._torch
-        B = int(idx.shape[0])
-        cols = list(range(len(self.elem_bytes))) if col_ids is None else list(col_ids)
         if out is None:
-            dev = torch.device("cuda", self.device)
-            out = [torch.empty((B, L * self.elem_bytes[c]), dtype=torch.uint8, device=dev) for c in cols]
-        gear_collect(self.handle, idx.data_ptr(), start.data_ptr(), B, L, col_ids,
+            return self._collect(idx, start, L, None if col_ids is None else list(col_ids), False, stream)
+        gear_collect(self.handle, idx.data_ptr(), start.data_ptr(), int(idx.shape[0]), L, col_ids,
                      [o.data_ptr() for o in out], self._stream(stream))
         return out
 
     def select_collect_fields(self, strategy, B, L, seed, fields=None, weights=False, stream=None):
-        """select_collect with the batch as {name: tensor[B, L, *shape]} views
-        of each column's dtype, as collect_fields returns them."""
-        names = [c.name for c in self.columns] if fields is None else list(fields)
-        ids = [self._index[n] for n in names]
-        idx, start, w, raw = self.select_collect(strategy, B, L, seed, weights=weights, col_ids=ids, stream=stream)
-        res = {}
-        for n, c, r in zip(names, ids, raw):
-            spec = self.columns[c]
-            res[n] = r.view(spec.torch_dtype()).view((B, L) + spec.shape)
-        return idx, start, w, res
+        """select_collect with the batch as {name: tensor[B, L, *shape]} of
+        each column's dtype, as collect_fields returns them."""
+        names = self._names if fields is None else list(fields)
+        ids = None if fields is None else [self._index[n] for n in names]
+        idx, start, w, batch = self._select_collect(strategy, B, L, seed, weights, ids, True, stream)
+        return idx, start, w, dict(zip(names, batch))
+
+    def _select_collect(self, strategy, B, L, seed, weights, col_ids, typed, stream):
+        return _result(self._native.select_collect(self.handle, self._plan, int(strategy), B, L, int(seed), weights,
+                                                   col_ids, typed, self.device, self._stream(stream)))
 
     def select_collect(self, strategy, B, L, seed, weights=False, col_ids=None, stream=None):
         """FIFO, LIFO or uniform selection and its gather in one launch:
         (idx, start, w, list of uint8 tensors [B, L*E_c]), equal to select()
         followed by collect()."""
-        torch = self._torch
-        dev = torch.device("cuda", self.device)
-        idx = torch.empty(B, dtype=torch.int64, device=dev)
-        start = torch.empty(B, dtype=torch.int32, device=dev)
-        w = torch.empty(B, dtype=torch.float32, device=dev) if weights else None
-        cols = list(range(len(self.elem_bytes))) if col_ids is None else list(col_ids)
-        out = [torch.empty((B, L * self.elem_bytes[c]), dtype=torch.uint8, device=dev) for c in cols]
-        gear_select_collect(self.handle, strategy, B, L, seed, idx.data_ptr(), start.data_ptr(),
-                            w.data_ptr() if w is not None else 0, col_ids, [o.data_ptr() for o in out],
-                            self._stream(stream))
-        return idx, start, w, out
+        return self._select_collect(strategy, B, L, seed, weights, None if col_ids is None else list(col_ids), False,
+                                    stream)
 
     def collect_fields(self, idx, start, L, fields=None, stream=None, out=None):
         """The batch as {name: tensor[B, L, *shape]} of each column's dtype
-        (Sec. 3.4: collect(indices, fields) handed over as tensors).  The
-        tensors are views of the byte batches that gear_collect writes (no
-        copy, no arithmetic); `out`, if given, is the dict of byte buffers
-        [B, L*E] to reuse."""
-        names = [c.name for c in self.columns] if fields is None else list(fields)
+        (Sec. 3.4: collect(indices, fields) handed over as tensors): the
+        buffers that gear_collect writes, with no copy.  `out`, if given, is
+        the dict of byte buffers [B, L*E] to reuse; the result then holds
+        views of them."""
+        names = self._names if fields is None else list(fields)
+        ids = None if fields is None else [self._index[n] for n in names]
+        if out is None:
+            return dict(zip(names, self._collect(idx, start, L, ids, True, stream)))
         ids = [self._index[n] for n in names]
-        raw = self.collect(idx, start, L, col_ids=ids, stream=stream,
-                           out=None if out is None else [out[n] for n in names])
+        raw = self.collect(idx, start, L, col_ids=ids, stream=stream, out=[out[n] for n in names])
         B = int(idx.shape[0])
         res = {}
         for n, c, r in zip(names, ids, raw):
@@ -493,8 +505,7 @@ class Table:
         return gear_table_find_column(self.handle, name)
 
     def update_priorities(self, idx, new_priorities, stream=None):
-        gear_update_priorities(self.handle, idx.data_ptr(), new_priorities.data_ptr(), int(idx.shape[0]),
-                               self._stream(stream))
+        _check(self._native.update(self.handle, idx, new_priorities, self._stream(stream)))
 
     def set_options(self, options):
         gear_table_set_options(self.handle, options)
@@ -526,21 +537,11 @@ class Table:
 
     def select_shard(self, G, g, totals, base, B, L, seed, stream=None):
         """Shard g's part of prioritized selection; returns (idx, start, sel_prio)."""
-        torch = self._torch
-        dev = torch.device("cuda", self.device)
-        idx = torch.empty(B, dtype=torch.int64, device=dev)
-        start = torch.empty(B, dtype=torch.int32, device=dev)
-        p = torch.empty(B, dtype=torch.int32, device=dev)
-        gear_select_shard(self.handle, G, g, totals.data_ptr(), base, B, L, seed, idx.data_ptr(), start.data_ptr(),
-                          p.data_ptr(), self._stream(stream))
-        return idx, start, p
+        return _result(self._native.select_shard(self.handle, int(G), int(g), totals, int(base), B, int(L), int(seed),
+                                                 self.device, self._stream(stream)))
 
     def is_weights(self, sel_prio, beta, stream=None):
-        torch = self._torch
-        w = torch.empty(int(sel_prio.shape[0]), dtype=torch.float32, device=torch.device("cuda", self.device))
-        gear_is_weights(self.handle, sel_prio.data_ptr(), int(sel_prio.shape[0]), beta, w.data_ptr(),
-                        self._stream(stream))
-        return w
+        return _result(self._native.is_weights(self.handle, sel_prio, beta, self.device, self._stream(stream)))
 
     def column_view(self, c):
         """Column c's blocks in place, [capacity, T*E_c] bytes: a torch uint8
