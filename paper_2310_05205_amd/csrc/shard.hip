@@ -61,16 +61,6 @@ __device__ __forceinline__ bool before(uint32_t pa, int64_t ia, uint32_t pb, int
     return pa > pb || (pa == pb && ia < ib);
 }
 
-__global__ void merge_fill_kernel(int32_t K, int64_t* __restrict__ idx, int32_t* __restrict__ start,
-                                  float* __restrict__ w, uint32_t* __restrict__ out_prio) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= K) return;
-    idx[k] = -1;
-    start[k] = 0;
-    if (w) w[k] = 0.0f;
-    if (out_prio) out_prio[k] = 0u;
-}
-
 // Merge of G sorted lists by ranks.  A workgroup takes a tile of
 // kMergeTile consecutive entries of list g, kMergeParts threads per entry.
 // The entries of another list h that come before a tile entry are all of h
@@ -84,51 +74,66 @@ __global__ void merge_fill_kernel(int32_t K, int64_t* __restrict__ idx, int32_t*
 // searched in global memory instead.  Binary searches by every thread
 // straight over global memory cost about eight times more load
 // instructions; one thread per entry leaves one wave per SIMD.
-constexpr int kMergeThreads = 256;
+//
+// A tile whose first entry already has K entries before it ends there: of G
+// full lists, all but about one tile in G.  The positions past the last
+// candidate are filled by further workgroups of the same launch.
+//
+// The kernel is a chain of memory round trips: the keys, three probe rounds
+// (16 lanes took four), the bracket, the results.  8 lists of 8192 took 15.2 us with 64-entry tiles,
+// 16 probe lanes, no early end and a fill launch of its own; now 9.2 (16 lists of
+// 16384: 56.8 -> 16.4).
+constexpr int kMergeThreads = 512;
 constexpr int kMergeParts = 4;                          // threads per tile entry
-constexpr int kMergeTile = kMergeThreads / kMergeParts;  // 64 entries
-constexpr int kMergeRound = 8;                           // lists per round: 2 * 8 searches, 4 per wave
+constexpr int kMergeTile = kMergeThreads / kMergeParts;  // 128 entries
+constexpr int kMergeRound = 8;                           // lists per round: 2 * 8 searches, 2 per wave
 constexpr int kListsPerPart = kMergeRound / kMergeParts;
-constexpr int kProbeLanes = 16;                          // lanes per cooperative search
-constexpr int kBracketCap = 1024;                        // bracket entries in LDS per round (12 KiB)
+constexpr int kProbeLanes = 32;                          // lanes per cooperative search
+constexpr int kBracketCap = 2048;                        // bracket entries in LDS per round (24 KiB)
+static_assert(kMergeThreads / kProbeLanes == 2 * kMergeRound, "one search per lane group");
 constexpr int kFillPerThread = kBracketCap / kMergeThreads;
 
-// Entries of list (ph, ih) of length K that come before (p, i), by the 16
-// lanes of group `grp` of the wave (lane `sub` within it).  Valid entries
-// form a sorted prefix, so "comes before" is true on a prefix of positions.
-// Each round probes 15 evenly spaced positions of the remaining range and
-// keeps the piece between the last probe that comes before and the first
-// that does not; a range of at most 16 positions is probed whole.  Every
-// lane of the wave must call this (the rounds use wave ballots).
-__device__ int group_count_before(const uint32_t* __restrict__ ph, const int64_t* __restrict__ ih, int K, uint32_t p,
-                                  int64_t i, bool active, int grp, int sub) {
-    int lo = 0, hi = K;  // the count lies in [lo, hi]
-    bool done = !active;
-    int count = 0;
-    while (__ballot(!done) != 0) {
-        const int n = hi - lo;
-        const bool whole = n <= kProbeLanes;
-        const int q = whole ? lo + sub : lo + ((sub + 1) * n) / kProbeLanes - 1;
-        bool pred = false;
-        if (!done && sub < (whole ? n : kProbeLanes - 1)) {
-            const int64_t iq = ih[q];  // both loads issued before either is used
-            const uint32_t pq = ph[q];
-            pred = (iq >= 0) & before(pq, iq, p, i);
-        }
-        const int c = __popcll((__ballot(pred) >> (grp * kProbeLanes)) & 0xFFFFull);
-        if (!done) {
-            if (whole) {
-                count = lo + c;
-                done = true;
-            } else {
-                const int nlo = c > 0 ? lo + (c * n) / kProbeLanes : lo;
-                const int nhi = c < kProbeLanes - 1 ? lo + ((c + 1) * n) / kProbeLanes - 1 : hi;
-                lo = nlo;
-                hi = nhi;
-            }
-        }
+// A search for the number of entries of a sorted list that come before one
+// entry, by the 32 lanes of group `grp` of the wave (lane `sub` within it).
+// Valid entries form a sorted prefix, so "comes before" is true on a prefix of
+// positions.  Each round probes 31 evenly spaced positions of the remaining
+// range and keeps the piece between the last probe that comes before and the
+// first that does not; a range of at most 32 positions is probed whole.  Four
+// probes per lane, which save a round, were slower (13.1 against 10.8 us for 8
+// lists of 8192): the rounds are bound by their scattered loads.
+struct Search {
+    int lo, hi;  // the count lies in [lo, hi]
+    bool done;
+};
+
+// Every lane of the wave must call this (it uses wave ballots).
+__device__ __forceinline__ void probe_round(Search& f, const uint32_t* __restrict__ ph, const int64_t* __restrict__ ih,
+                                            uint32_t p, int64_t i, int grp, int sub) {
+    const int n = f.hi - f.lo;
+    const bool whole = n <= kProbeLanes;
+    const int q = whole ? f.lo + sub : f.lo + ((sub + 1) * n) / kProbeLanes - 1;
+    bool pred = false;
+    if (!f.done && sub < (whole ? n : kProbeLanes - 1)) {
+        const int64_t iq = ih[q];  // both loads issued before either is used
+        const uint32_t pq = ph[q];
+        pred = (iq >= 0) & before(pq, iq, p, i);
     }
-    return count;
+    const int c = __popc((uint32_t)(__ballot(pred) >> (grp * kProbeLanes)));
+    if (f.done) return;
+    if (whole) {
+        f.lo = f.hi = f.lo + c;
+        f.done = true;
+    } else {
+        const int lo = f.lo;
+        f.lo = c > 0 ? lo + (c * n) / kProbeLanes : lo;
+        f.hi = c < kProbeLanes - 1 ? lo + ((c + 1) * n) / kProbeLanes - 1 : f.hi;
+    }
+}
+
+__device__ __forceinline__ int finish_search(Search& f, const uint32_t* __restrict__ ph, const int64_t* __restrict__ ih,
+                                             uint32_t p, int64_t i, int grp, int sub) {
+    while (__ballot(!f.done) != 0) probe_round(f, ph, ih, p, i, grp, sub);
+    return f.lo;
 }
 
 __global__ __launch_bounds__(kMergeThreads) void merge_kernel(const uint32_t* __restrict__ prio,
@@ -138,14 +143,42 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(const uint32_t* __
                                                               uint32_t* __restrict__ out_prio) {
     __shared__ uint32_t s_p[kBracketCap];
     __shared__ int64_t s_i[kBracketCap];
-    __shared__ int s_lo[kMergeRound], s_hi[kMergeRound], s_off[kMergeRound];
-    __shared__ int s_steps;
+    __shared__ int s_lo[kMergeRound], s_hi[kMergeRound];
+    __shared__ int s_found;
     __shared__ uint32_t s_kp[2];
     __shared__ int64_t s_ki[2];
     const int tiles = (K + kMergeTile - 1) / kMergeTile;
-    const int g = (int)(blockIdx.x / tiles);
+    const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
+    const int grp = lane / kProbeLanes, sub = lane % kProbeLanes;
+    const int search = wave * (64 / kProbeLanes) + grp;  // 0 .. 2 * kMergeRound - 1
+    // Tiles in the order of their position in the lists, so that those that end
+    // early come last; then the filling workgroups.
+    const int tile = (int)(blockIdx.x / (unsigned)G), g = (int)(blockIdx.x % (unsigned)G);
+    if (tile >= tiles) {
+        // Positions from the candidates' number on, kMergeThreads of them here.
+        bool full = false;  // a list with K candidates leaves nothing to fill
+        for (int h = threadIdx.x; h < G; h += kMergeThreads) full = full || gidx[(int64_t)h * K + K - 1] >= 0;
+        if (threadIdx.x == 0) s_found = 0;
+        if (__syncthreads_or(full)) return;
+        int found = 0;  // candidates of the lists that this group counts
+        for (int h0 = 0; h0 < G; h0 += 2 * kMergeRound) {
+            const bool act = h0 + search < G;
+            const int64_t at = (int64_t)(act ? h0 + search : 0) * K;
+            Search f{0, act ? K : 0, !act};
+            found += finish_search(f, prio + at, gidx + at, 0u, INT64_MAX, grp, sub);
+        }
+        if (sub == 0) atomicAdd(&s_found, found);
+        __syncthreads();
+        const int64_t k = (int64_t)(blockIdx.x - (unsigned)(G * tiles)) * kMergeThreads + threadIdx.x;
+        if (k >= K || k < s_found) return;
+        idx[k] = -1;
+        start[k] = 0;
+        if (w) w[k] = 0.0f;
+        if (out_prio) out_prio[k] = 0u;
+        return;
+    }
     const int entry = (int)threadIdx.x / kMergeParts, part = (int)threadIdx.x % kMergeParts;
-    const int j = (int)(blockIdx.x % tiles) * kMergeTile + entry;
+    const int j = tile * kMergeTile + entry;
     const int64_t at = (int64_t)g * K + j;
     const int64_t i = j < K ? gidx[at] : -1;
     const uint32_t p = j < K ? prio[at] : 0u;
@@ -161,48 +194,47 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(const uint32_t* __
         s_ki[1] = i;
     }
     __syncthreads();
-    const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
-    const int grp = lane / kProbeLanes, sub = lane % kProbeLanes;
-    const int search = wave * (64 / kProbeLanes) + grp;  // 0 .. 2 * kMergeRound - 1
     const int su = search >> 1, end = search & 1;         // list in the round; 0: first entry, 1: last entry
     int count = 0;
+    int64_t first_place = (int64_t)tile * kMergeTile;  // of the tile's first entry, lists so far
     for (int h0 = 0; h0 < G; h0 += kMergeRound) {
         {
             const int h = h0 + su;
             const bool act = h < G && h != g;
-            const int r = group_count_before(prio + (int64_t)(act ? h : 0) * K, gidx + (int64_t)(act ? h : 0) * K, K,
-                                             s_kp[end], s_ki[end], act, grp, sub);
-            if (act && sub == 0) (end ? s_hi : s_lo)[su] = r;
+            const int64_t base = (int64_t)(act ? h : 0) * K;
+            Search f{0, act ? K : 0, !act};
+            probe_round(f, prio + base, gidx + base, s_kp[end], s_ki[end], grp, sub);
+            // The first round already bounds the first entry's place from
+            // below, closely enough to end most tiles that will not count.
+            if (sub == 0) (end ? s_hi : s_lo)[su] = f.lo;
+            __syncthreads();
+            int64_t least = first_place;
+#pragma unroll
+            for (int u = 0; u < kMergeRound; u++) least += s_lo[u];
+            if (least >= K) return;  // the same for the whole workgroup
+            __syncthreads();
+            const int r = finish_search(f, prio + base, gidx + base, s_kp[end], s_ki[end], grp, sub);
+            if (sub == 0) (end ? s_hi : s_lo)[su] = r;
         }
         __syncthreads();
-        if (threadIdx.x == 0) {
-            int used = 0, widest = 0;
-            for (int u = 0; u < kMergeRound; u++) {
-                const int h = h0 + u;
-                if (h >= G || h == g) {
-                    s_lo[u] = s_hi[u] = 0;
-                    s_off[u] = 0;
-                    continue;
-                }
-                const int wdt = s_hi[u] - s_lo[u];
-                widest = wdt > widest ? wdt : widest;
-                if (used + wdt <= kBracketCap) {
-                    s_off[u] = used;
-                    used += wdt;
-                } else {
-                    s_off[u] = -1;
-                }
-            }
-            s_steps = 32 - __clz((unsigned)widest);  // halvings that empty the widest bracket
-        }
-        __syncthreads();
+        // Every thread lays out the round's brackets for itself: entries of
+        // list u go to LDS at r_off[u], or stay in global memory (-1) when they
+        // no longer fit.
         int r_off[kMergeRound], r_lo[kMergeRound], r_w[kMergeRound];
+        int used = 0, widest = 0;
 #pragma unroll
         for (int u = 0; u < kMergeRound; u++) {
-            r_off[u] = s_off[u];
-            r_lo[u] = s_lo[u];
-            r_w[u] = s_hi[u] - s_lo[u];
+            const int h = h0 + u;
+            const bool other = h < G && h != g;
+            r_lo[u] = other ? s_lo[u] : 0;
+            r_w[u] = other ? s_hi[u] - s_lo[u] : 0;
+            widest = r_w[u] > widest ? r_w[u] : widest;
+            r_off[u] = used + r_w[u] <= kBracketCap ? used : -1;
+            used += r_off[u] >= 0 ? r_w[u] : 0;
+            first_place += r_lo[u];
         }
+        if (first_place >= K) return;  // the same for the whole workgroup
+        const int steps = 32 - __clz((unsigned)widest);  // halvings that empty the widest bracket
         {
             // Every bracket entry of the round, kFillPerThread per thread at
             // most: all loads are issued before the first LDS store.
@@ -243,7 +275,6 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(const uint32_t* __
                 lo[v] = 0;
                 hi[v] = r_w[part + v * kMergeParts];
             }
-            const int steps = s_steps;
             for (int step = 0; step < steps; step++) {
 #pragma unroll
                 for (int v = 0; v < kListsPerPart; v++) {
@@ -281,8 +312,6 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(const uint32_t* __
     if (w) w[place] = 1.0f;
     if (out_prio) out_prio[place] = p;
 }
-
-unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
 }  // namespace gear
@@ -366,15 +395,11 @@ extern "C" int gear_topk_merge(const uint32_t* d_prio, const int64_t* d_gidx, in
         return fail(GEAR_E_INVAL, "gear_topk_merge: NULL pointer argument");
     (void)hipGetLastError();  // an error pending from an earlier HIP call is not this call's
     hipStream_t s = static_cast<hipStream_t>(stream);
-    hipLaunchKernelGGL(gear::merge_fill_kernel, dim3(gear::blocks_for(K)), dim3(256), 0, s, K, d_idx, d_start,
-                       d_weights, d_out_prio);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) {
-        const int64_t tiles = ((int64_t)K + gear::kMergeTile - 1) / gear::kMergeTile;
-        hipLaunchKernelGGL(gear::merge_kernel, dim3((unsigned)(G * tiles)), dim3(gear::kMergeThreads), 0, s, d_prio, d_gidx,
-                           G, K, (uint64_t)(T - L + 1), seed, d_idx, d_start, d_weights, d_out_prio);
-        e = hipGetLastError();
-    }
+    const int64_t tiles = ((int64_t)K + gear::kMergeTile - 1) / gear::kMergeTile;
+    const int64_t fill = ((int64_t)K + gear::kMergeThreads - 1) / gear::kMergeThreads;
+    hipLaunchKernelGGL(gear::merge_kernel, dim3((unsigned)(G * tiles + fill)), dim3(gear::kMergeThreads), 0, s, d_prio,
+                       d_gidx, G, K, (uint64_t)(T - L + 1), seed, d_idx, d_start, d_weights, d_out_prio);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "gear_topk_merge: launch");
     return GEAR_OK;
 }
