@@ -19,14 +19,15 @@
 // call's decisions are a few integer operations per index.  The device keeps
 // a copy of the commit-order ring (FIFO, LIFO and uniform selection read it)
 // and a committed flag per slot (priority updates of other slots are
-// dropped).  Index lists reach the device through the table's ring of
-// pinned, mapped staging slots, which the kernels read in place; a slot is
-// refilled only after its last reader has run, so the host waits only when
-// every slot is still in use.
+// dropped).  An index list of a few runs of consecutive slots (what FIFO
+// removal allocates) travels in the kernels' arguments; any other reaches the
+// device through the table's ring of pinned, mapped staging slots, which the
+// kernels read in place; a slot is refilled only after its last reader has
+// run, so the host waits only when every slot is still in use.
 //
-// Rows are written into their slots by one scatter kernel per column (any
-// slot order), or, from pageable host memory that kernels cannot read, by
-// one copy per run of consecutive slots.
+// Rows of a few runs of consecutive slots are copied by one launch for all
+// columns, other lists by one scatter kernel per column (any slot order), and
+// rows in pageable host memory, which kernels cannot read, by one copy per run.
 #include <algorithm>
 #include <cstring>
 #include <new>
@@ -36,23 +37,154 @@
 namespace gear {
 namespace {
 
-__global__ void evict_kernel(const int64_t* __restrict__ victims, int64_t n, uint32_t* __restrict__ prio,
-                             uint8_t* __restrict__ committed) {
+// A list of slots: in memory, or as runs of consecutive slots (ascending or
+// descending) in the kernel's arguments.  A kernel that reads a list from pinned
+// host memory delays the next kernel by about 5 us; one that finds it in its
+// arguments does not.
+constexpr int kMaxRuns = 8;
+struct SlotList {
+    const int64_t* idx;         // the list, or NULL for the runs
+    int64_t first[kMaxRuns];    // first slot of each run
+    int64_t end[kMaxRuns];      // list position behind it; past the last run INT64_MAX
+    int32_t step[kMaxRuns];     // 1 or -1
+
+    __device__ int64_t slot(int64_t j) const {
+        if (idx != nullptr) return idx[j];
+        int64_t at = first[0] + j * step[0];
+#pragma unroll
+        for (int r = 1; r < kMaxRuns; r++)
+            if (j >= end[r - 1]) at = first[r] + (j - end[r - 1]) * step[r];
+        return at;
+    }
+};
+
+// The list idx[0 .. n) as at most kMaxRuns runs; false if it has more.
+// ascending: only runs of step 1.
+bool find_runs(const int64_t* idx, int64_t n, bool ascending, SlotList& list, int& runs) {
+    list.idx = nullptr;
+    runs = 0;
+    for (int64_t j = 0; j < n;) {
+        if (runs == kMaxRuns) return false;
+        const int step = !ascending && j + 1 < n && idx[j + 1] == idx[j] - 1 ? -1 : 1;
+        int64_t k = j + 1;
+        while (k < n && idx[k] == idx[k - 1] + step) k++;
+        list.first[runs] = idx[j];
+        list.step[runs] = step;
+        list.end[runs] = k;
+        runs++;
+        j = k;
+    }
+    for (int r = runs; r < kMaxRuns; r++) {
+        list.first[r] = 0;
+        list.step[r] = 1;
+        list.end[r] = INT64_MAX;
+    }
+    if (runs > 0) list.end[runs - 1] = INT64_MAX;
+    return true;
+}
+
+__global__ void evict_kernel(SlotList victims, int64_t n, uint32_t* __restrict__ prio, uint8_t* __restrict__ committed) {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= n) return;
-    const int64_t i = victims[j];
+    const int64_t i = victims.slot(j);
     prio[i] = 0u;
     committed[i] = 0;
 }
 
 // Commit j of this chunk takes commit-order position pos0 + j (mod N).
-__global__ void commit_kernel(const int64_t* __restrict__ idx, const uint32_t* __restrict__ p, int64_t n,
-                              int64_t pos0, int64_t N, int32_t* __restrict__ order, uint32_t* __restrict__ prio,
+__global__ void commit_kernel(SlotList list, const uint32_t* __restrict__ p, int64_t n, int64_t pos0, int64_t N,
+                              int32_t* __restrict__ order, uint32_t* __restrict__ prio,
                               uint8_t* __restrict__ committed) {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= n) return;
-    const int64_t i = idx[j];
+    const int64_t i = list.slot(j);
     prio[i] = p[j];
+    committed[i] = 1;
+    int64_t pos = pos0 + j;
+    if (pos >= N) pos -= N;
+    order[pos] = (int32_t)i;
+}
+
+// Contiguous copies, all in one launch: a workgroup of one wave takes a piece
+// of 1 KiB of one segment's destination, 16 bytes per lane, cut at 16-byte
+// addresses of the destination so that every store but a segment's first and
+// last is whole and aligned; sources may start at any byte.  Both sides are read
+// and written once and non-temporally, as in the row scatter.  Bound by HBM when
+// large: 217 MB of rows into a ring 89.6 -> 70.2 us (6.2 TB/s read and written;
+// 256 lanes per workgroup 75.3, two elements per lane 72.4), through the index
+// manager 89.8 -> 77.8; and by its one launch when small: 64 such rows through
+// the manager 30.1 -> 17.4.
+constexpr int kSegThreads = 64;
+constexpr int kSegElems = 1;   // 16-byte elements per lane
+constexpr int64_t kSegPiece = (int64_t)kSegThreads * kSegElems * 16;
+constexpr int kMaxSegments = 40;  // per launch
+
+typedef unsigned int seg_elem __attribute__((ext_vector_type(4)));
+typedef seg_elem seg_src __attribute__((aligned(1)));
+
+struct SegmentArgs {
+    uint32_t task0[kMaxSegments];  // first workgroup of each segment; UINT32_MAX past the last
+    Segment seg[kMaxSegments];
+};
+
+struct WordArgs {
+    uint32_t task0;  // first workgroup that writes words
+    int32_t n;
+    uint32_t* dst;
+    int64_t at, N;
+    uint32_t words[kInlineWords];
+};
+
+__device__ __forceinline__ void copy_piece(const SegmentArgs& a) {
+    // The segment: the last one whose first workgroup is not past this one.
+    int k = 0;
+#pragma unroll 1
+    for (int g = 8; g < kMaxSegments && a.task0[g] <= blockIdx.x; g += 8) k = g;
+#pragma unroll
+    for (int r = 1; r < 8; r++) k += a.task0[(k & ~7) + r] <= blockIdx.x ? 1 : 0;
+    const Segment g = a.seg[k];
+    // Piece q: destination bytes [lo, hi) of the segment, from the 16-byte
+    // address at or before its start.
+    const int64_t lead = (int64_t)(reinterpret_cast<uintptr_t>(g.dst) & 15);
+    const int64_t lo = (int64_t)(blockIdx.x - a.task0[k]) * kSegPiece - lead;
+    seg_elem v[kSegElems];
+#pragma unroll
+    for (int u = 0; u < kSegElems; u++) {
+        const int64_t o = lo + ((int64_t)u * kSegThreads + threadIdx.x) * 16;
+        if (o >= 0 && o + 16 <= g.bytes)
+            v[u] = __builtin_nontemporal_load(reinterpret_cast<const seg_src*>(g.src + o));
+    }
+#pragma unroll
+    for (int u = 0; u < kSegElems; u++) {
+        const int64_t o = lo + ((int64_t)u * kSegThreads + threadIdx.x) * 16;
+        if (o >= 0 && o + 16 <= g.bytes) {
+            __builtin_nontemporal_store(v[u], reinterpret_cast<seg_elem*>(g.dst + o));
+        } else {
+            for (int64_t e = o < 0 ? 0 : o; e < o + 16 && e < g.bytes; e++) g.dst[e] = g.src[e];
+        }
+    }
+}
+
+__global__ __launch_bounds__(kSegThreads) void copy_segments_kernel(SegmentArgs a) { copy_piece(a); }
+
+__global__ __launch_bounds__(kSegThreads) void copy_segments_words_kernel(SegmentArgs a, WordArgs w) {
+    if (blockIdx.x < w.task0) {
+        copy_piece(a);
+        return;
+    }
+    const int j = (int)(blockIdx.x - w.task0) * kSegThreads + (int)threadIdx.x;
+    if (j >= w.n) return;
+    const int64_t pos = w.at + j;
+    w.dst[pos >= w.N ? pos - w.N : pos] = w.words[j];
+}
+
+// A commit of up to kInlineWords priorities that lie in pageable host memory.
+__global__ void commit_words_kernel(SlotList list, WordArgs w, int64_t pos0, int64_t N, int32_t* __restrict__ order,
+                                    uint32_t* __restrict__ prio, uint8_t* __restrict__ committed) {
+    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= w.n) return;
+    const int64_t i = list.slot(j);
+    prio[i] = w.words[j];
     committed[i] = 1;
     int64_t pos = pos0 + j;
     if (pos >= N) pos -= N;
@@ -150,6 +282,13 @@ hipError_t launch_rows(const int64_t* d_idx, int64_t n, const uint8_t* src, uint
     return hipSuccess;
 }
 
+__global__ void copy_list_kernel(const int64_t* __restrict__ src, int64_t n, int64_t* __restrict__ dst) {
+    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j < n) dst[j] = src[j];
+}
+
+unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
+
 // Whether a kernel on the table's device can read `p` (device memory, or
 // pinned / mapped host memory); pageable host memory cannot.
 bool device_readable(const void* p) {
@@ -160,42 +299,6 @@ bool device_readable(const void* p) {
     }
     return a.type == hipMemoryTypeDevice || a.type == hipMemoryTypeHost || a.type == hipMemoryTypeManaged;
 }
-
-// One slot of the table's pinned staging ring: a host list is copied into
-// it by the CPU and read in place by the kernels of one chunk.  A slot is
-// refilled only after the event recorded behind its last reader, so the
-// host waits only when every slot is still being read.
-struct PinSlot {
-    int k;
-    int64_t* h_idx;
-    uint32_t* h_prio;
-    const int64_t* d_idx;    // device addresses of the same memory
-    const uint32_t* d_prio;
-};
-
-hipError_t acquire_slot(Table& t, PinSlot& ps) {
-    ps.k = t.pin_next;
-    t.pin_next = (ps.k + 1) % kStageSlots;
-    const hipError_t e = hipEventSynchronize(t.pin_free[ps.k]);
-    if (e != hipSuccess) return e;
-    const int64_t off = (int64_t)ps.k * kStageSlotBytes;
-    const int64_t prio_off = off + kStageRows * (int64_t)sizeof(int64_t);
-    ps.h_idx = reinterpret_cast<int64_t*>(t.pin_host + off);
-    ps.h_prio = reinterpret_cast<uint32_t*>(t.pin_host + prio_off);
-    ps.d_idx = reinterpret_cast<const int64_t*>(t.pin_dev + off);
-    ps.d_prio = reinterpret_cast<const uint32_t*>(t.pin_dev + prio_off);
-    return hipSuccess;
-}
-
-// Call after enqueuing the last kernel that reads the slot.
-hipError_t release_slot(Table& t, const PinSlot& ps, hipStream_t s) { return hipEventRecord(t.pin_free[ps.k], s); }
-
-__global__ void copy_list_kernel(const int64_t* __restrict__ src, int64_t n, int64_t* __restrict__ dst) {
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < n) dst[j] = src[j];
-}
-
-unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 // Releases one victim by the removal strategy (host state only).
 // Positions in the rings are below N and counts at most N, so a sum of the
@@ -219,6 +322,71 @@ int64_t release_victim(Table& t) {
 }
 
 }  // namespace
+
+Source source_kind(const void* p, int device) {
+    hipPointerAttribute_t a;
+    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return Source::kPageable;
+    }
+    if (a.type == hipMemoryTypeUnregistered) return Source::kPageable;
+    if (a.type == hipMemoryTypeDevice && a.device == device) return Source::kDevice;
+    return a.type == hipMemoryTypeHost ? Source::kPinned : Source::kOther;
+}
+
+hipError_t acquire_slot(Table& t, PinSlot& ps) {
+    ps.k = t.pin_next;
+    t.pin_next = (ps.k + 1) % kStageSlots;
+    const hipError_t e = hipEventSynchronize(t.pin_free[ps.k]);
+    if (e != hipSuccess) return e;
+    const int64_t off = (int64_t)ps.k * kStageSlotBytes;
+    const int64_t prio_off = off + kStageRows * (int64_t)sizeof(int64_t);
+    ps.h_idx = reinterpret_cast<int64_t*>(t.pin_host + off);
+    ps.h_prio = reinterpret_cast<uint32_t*>(t.pin_host + prio_off);
+    ps.d_idx = reinterpret_cast<const int64_t*>(t.pin_dev + off);
+    ps.d_prio = reinterpret_cast<const uint32_t*>(t.pin_dev + prio_off);
+    return hipSuccess;
+}
+
+hipError_t release_slot(Table& t, const PinSlot& ps, hipStream_t s) { return hipEventRecord(t.pin_free[ps.k], s); }
+
+hipError_t launch_segments(const Segment* seg, int n, const WordTail* tail, hipStream_t s) {
+    int k = 0;
+    do {
+        SegmentArgs a{};
+        for (int j = 0; j < kMaxSegments; j++) a.task0[j] = UINT32_MAX;
+        int64_t tasks = 0;
+        int used = 0;
+        for (; k < n && used < kMaxSegments; k++) {
+            if (seg[k].bytes <= 0) continue;
+            const int64_t lead = (int64_t)(reinterpret_cast<uintptr_t>(seg[k].dst) & 15);
+            const int64_t more = (lead + seg[k].bytes + kSegPiece - 1) / kSegPiece;
+            if (used > 0 && tasks + more > 0x7FFFFFF0) break;    // the next launch's
+            if (more > 0x7FFFFFF0) return hipErrorInvalidValue;  // above 2 TiB: more than any device holds
+            a.task0[used] = (uint32_t)tasks;
+            a.seg[used++] = seg[k];
+            tasks += more;
+        }
+        if (k == n && tail != nullptr) {  // with the last segments
+            WordArgs w;
+            w.task0 = (uint32_t)tasks;
+            w.n = tail->n;
+            w.dst = tail->dst;
+            w.at = tail->at;
+            w.N = tail->N;
+            std::memcpy(w.words, tail->words, sizeof(uint32_t) * (size_t)tail->n);
+            tasks += (tail->n + kSegThreads - 1) / kSegThreads;
+            hipLaunchKernelGGL(copy_segments_words_kernel, dim3((unsigned)tasks), dim3(kSegThreads), 0, s, a, w);
+        } else if (used > 0) {
+            hipLaunchKernelGGL(copy_segments_kernel, dim3((unsigned)tasks), dim3(kSegThreads), 0, s, a);
+        } else {
+            continue;
+        }
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    } while (k < n);
+    return hipSuccess;
+}
 
 void free_index_manager(Table& t) {
     (void)hipFree(t.order);
@@ -253,6 +421,25 @@ int write_rows(Table& t, int64_t n, const int64_t* idx, const void* const* col_s
         }
     }
     if (!any_kernel) return GEAR_OK;
+    SlotList list;
+    int runs = 0;
+    if (find_runs(idx, n, true, list, runs)) {
+        Segment seg[GEAR_MAX_COLUMNS * kMaxRuns];
+        int count = 0;
+        for (int c = 0; c < t.ncols; c++) {
+            if (!kernel_path[(size_t)c]) continue;
+            const int64_t rb = (int64_t)t.T * t.elem_bytes[c];
+            int64_t r0 = 0;
+            for (int r = 0; r < runs; r++) {
+                const int64_t r1 = r + 1 < runs ? list.end[r] : n;
+                seg[count++] = {static_cast<const uint8_t*>(col_src[c]) + (size_t)r0 * rb,
+                                t.col_dev[c] + (size_t)list.first[r] * rb, (r1 - r0) * rb};
+                r0 = r1;
+            }
+        }
+        const hipError_t e = launch_segments(seg, count, nullptr, s);
+        return e == hipSuccess ? GEAR_OK : hip_fail(e, "row copy launch");
+    }
     // The slot list moves to HBM once per chunk for all columns.
     for (int64_t off = 0; off < n; off += kStageRows) {
         const int64_t cnt = std::min(n - off, kStageRows);
@@ -383,16 +570,27 @@ extern "C" int gear_allocate(gear_table* h, int64_t n, int64_t* idx_out, void* s
         idx_out[r] = i;
     }
     // Victims become unselectable before the caller writes into any slot.
-    for (size_t off = 0; off < victims.size(); off += (size_t)gear::kStageRows) {
-        const int64_t cnt = (int64_t)std::min(victims.size() - off, (size_t)gear::kStageRows);
-        gear::PinSlot ps;
-        hipError_t e = gear::acquire_slot(*t, ps);
-        if (e != hipSuccess) return hip_fail(e, "gear_allocate: staging victims");
-        std::memcpy(ps.h_idx, victims.data() + off, sizeof(int64_t) * (size_t)cnt);
-        hipLaunchKernelGGL(gear::evict_kernel, dim3(gear::blocks_for(cnt)), dim3(256), 0, s, ps.d_idx, cnt,
-                           t->priority, t->committed);
-        if ((e = hipGetLastError()) == hipSuccess) e = gear::release_slot(*t, ps, s);
+    gear::SlotList list;
+    int runs = 0;
+    if (!victims.empty() && gear::find_runs(victims.data(), (int64_t)victims.size(), false, list, runs)) {
+        const int64_t cnt = (int64_t)victims.size();
+        hipLaunchKernelGGL(gear::evict_kernel, dim3(gear::blocks_for(cnt)), dim3(256), 0, s, list, cnt, t->priority,
+                           t->committed);
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, "gear_allocate: launch");
+    } else {
+        for (size_t off = 0; off < victims.size(); off += (size_t)gear::kStageRows) {
+            const int64_t cnt = (int64_t)std::min(victims.size() - off, (size_t)gear::kStageRows);
+            gear::PinSlot ps;
+            hipError_t e = gear::acquire_slot(*t, ps);
+            if (e != hipSuccess) return hip_fail(e, "gear_allocate: staging victims");
+            std::memcpy(ps.h_idx, victims.data() + off, sizeof(int64_t) * (size_t)cnt);
+            list.idx = ps.d_idx;
+            hipLaunchKernelGGL(gear::evict_kernel, dim3(gear::blocks_for(cnt)), dim3(256), 0, s, list, cnt,
+                               t->priority, t->committed);
+            if ((e = hipGetLastError()) == hipSuccess) e = gear::release_slot(*t, ps, s);
+            if (e != hipSuccess) return hip_fail(e, "gear_allocate: launch");
+        }
     }
     if (!victims.empty()) t->cdf_dirty = true;
     return GEAR_OK;
@@ -421,20 +619,39 @@ extern "C" int gear_commit(gear_table* h, int64_t n, const int64_t* idx, const u
     const bool prio_in_place = gear::device_readable(priorities);
     for (int64_t off = 0; off < n; off += gear::kStageRows) {
         const int64_t cnt = std::min(n - off, gear::kStageRows);
-        gear::PinSlot ps;
-        hipError_t e = gear::acquire_slot(*t, ps);
-        if (e != hipSuccess) return hip_fail(e, "gear_commit: staging");
-        std::memcpy(ps.h_idx, idx + off, sizeof(int64_t) * (size_t)cnt);
+        gear::SlotList list;
+        int runs = 0;
+        const bool in_args = gear::find_runs(idx + off, cnt, false, list, runs);
         const uint32_t* p = priorities + off;
-        if (!prio_in_place) {
-            std::memcpy(ps.h_prio, p, sizeof(uint32_t) * (size_t)cnt);
-            p = ps.d_prio;
-        }
         const int64_t pos0 = gear::wrap(t->ord_head + t->n_committed, t->N);
-        hipLaunchKernelGGL(gear::commit_kernel, dim3(gear::blocks_for(cnt)), dim3(256), 0, s, ps.d_idx, p, cnt, pos0,
-                           t->N, t->order, t->priority, t->committed);
-        if ((e = hipGetLastError()) == hipSuccess) e = gear::release_slot(*t, ps, s);
-        if (e != hipSuccess) return hip_fail(e, "gear_commit: launch");
+        gear::PinSlot ps;
+        hipError_t e = hipSuccess;
+        if (in_args && !prio_in_place && cnt <= gear::kInlineWords) {  // nothing for the kernel to fetch from the host
+            gear::WordArgs w;
+            w.n = (int32_t)cnt;
+            std::memcpy(w.words, p, sizeof(uint32_t) * (size_t)cnt);
+            hipLaunchKernelGGL(gear::commit_words_kernel, dim3(gear::blocks_for(cnt)), dim3(256), 0, s, list, w, pos0,
+                               t->N, t->order, t->priority, t->committed);
+            if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "gear_commit: launch");
+        } else {
+            if (!in_args || !prio_in_place) {
+                e = gear::acquire_slot(*t, ps);
+                if (e != hipSuccess) return hip_fail(e, "gear_commit: staging");
+                if (!in_args) {
+                    std::memcpy(ps.h_idx, idx + off, sizeof(int64_t) * (size_t)cnt);
+                    list.idx = ps.d_idx;
+                }
+                if (!prio_in_place) {
+                    std::memcpy(ps.h_prio, p, sizeof(uint32_t) * (size_t)cnt);
+                    p = ps.d_prio;
+                }
+            }
+            hipLaunchKernelGGL(gear::commit_kernel, dim3(gear::blocks_for(cnt)), dim3(256), 0, s, list, p, cnt, pos0, t->N,
+                               t->order, t->priority, t->committed);
+            e = hipGetLastError();
+            if (e == hipSuccess && (!in_args || !prio_in_place)) e = gear::release_slot(*t, ps, s);
+            if (e != hipSuccess) return hip_fail(e, "gear_commit: launch");
+        }
         int64_t pos = pos0;
         for (int64_t j = off; j < off + cnt; j++) {
             t->slot_state[(size_t)idx[j]] = gear::kSlotCommitted;

@@ -164,6 +164,42 @@ SimpleDraws simple_draws(const Table& t, int32_t strategy, int32_t L, uint64_t s
 // slot into the sum tree the last scan filled.
 hipError_t launch_scatter(Table& t, const int64_t* idx, const uint32_t* newp, int32_t B, bool maintain_tree,
                           hipStream_t s);
+// Contiguous copies that one launch makes together.
+struct Segment {
+    const uint8_t* src;
+    uint8_t* dst;
+    int64_t bytes;
+};
+// A short list of words on the host that the same launch writes to positions
+// (at + j) mod N of `dst`; it travels in the kernel's arguments.
+constexpr int kInlineWords = 512;
+struct WordTail {
+    const uint32_t* words;  // host, n of them
+    int n;                  // at most kInlineWords
+    uint32_t* dst;
+    int64_t at, N;
+};
+// Copies every segment (device-readable sources and destinations, which do not
+// overlap); empty ones are skipped.  `tail` may be NULL.
+hipError_t launch_segments(const Segment* seg, int n, const WordTail* tail, hipStream_t s);
+// Where a source lives: memory of `device`, page-locked or pageable host memory,
+// or anything else (managed memory, another device).
+enum class Source { kDevice, kPinned, kPageable, kOther };
+Source source_kind(const void* p, int device);
+// One slot of the pinned staging ring: a host list is copied into it by the CPU
+// and read in place by the kernels of one chunk.  A slot is refilled only
+// after the event recorded behind its last reader, so the host waits only when
+// every slot is still being read.
+struct PinSlot {
+    int k;
+    int64_t* h_idx;
+    uint32_t* h_prio;
+    const int64_t* d_idx;    // device addresses of the same memory
+    const uint32_t* d_prio;
+};
+hipError_t acquire_slot(Table& t, PinSlot& ps);
+// Call after enqueuing the last kernel that reads the slot.
+hipError_t release_slot(Table& t, const PinSlot& ps, hipStream_t s);
 // Index manager: release the memory of a managed table's extra arrays.
 void free_index_manager(Table& t);
 // Managed insertion used by gear_insert: allocate n, copy the rows into the
