@@ -33,6 +33,8 @@ constexpr int32_t kSmallMaxB = GEAR_SMALL_SELECT_MAX_B;  // ... for batches up t
 // TopK: at most this many workgroups per digit pass.
 constexpr int kTopkMaxGrid = 256;
 constexpr int kTopkBins = 4096;       // bins of one TopK digit pass (12-bit digits)
+constexpr int kTopkRows0 = 4;         // rows of pass 0's global histogram, at most
+constexpr int kTopkHistRows = kTopkRows0 + 2;
 constexpr int kTopkStateWords = 32;   // TopK selection states after 0 .. 3 digit passes
 constexpr int kTopkMaxK = GEAR_MAX_TOPK;
 // Host index and priority lists (row writes, allocation, commits) are
@@ -80,7 +82,7 @@ struct Table {
     uint32_t options = 0;             // GEAR_OPT_* bits
 
     // TopK scratch (fixed sizes).
-    uint32_t* topk_hist = nullptr;    // [3][kTopkBins] digit histograms, zero between calls
+    uint32_t* topk_hist = nullptr;    // [kTopkHistRows][kTopkBins] digit histograms, zero between calls
     uint32_t* topk_state = nullptr;   // [kTopkStateWords] selection states after 0 .. 3 digit passes
     uint32_t* topk_local = nullptr;   // [3][kTopkMaxGrid][kTopkBins] per-workgroup suffix sums of each digit pass
     // Index manager (allocate / commit insertion), off for ring tables.  The
@@ -108,7 +110,7 @@ struct Table {
     hipEvent_t pin_free[kStageSlots] = {};  // recorded after the last kernel that reads each slot
     int pin_next = 0;                 // slot the next chunk uses
 
-    uint64_t* topk_keys = nullptr;    // [kTopkMaxK] selected keys (p << 32 | ~slot), equal priorities in slot order
+    uint64_t* topk_keys = nullptr;    // selected keys: uint32 priorities [kTopkMaxK], then their slots
 };
 
 // Thread-local error reporting.

@@ -287,7 +287,7 @@ int create_table(const int64_t* elem_bytes, int32_t ncols, int64_t capacity, int
             free_table(t);
             return hip_fail(e, "gear_table_create: staging events");
         }
-    if ((e = dmalloc(hook, &t->topk_hist, sizeof(uint32_t) * 3 * gear::kTopkBins)) != hipSuccess ||
+    if ((e = dmalloc(hook, &t->topk_hist, sizeof(uint32_t) * gear::kTopkHistRows * gear::kTopkBins)) != hipSuccess ||
         (e = dmalloc(hook, &t->topk_state, sizeof(uint32_t) * gear::kTopkStateWords)) != hipSuccess ||
         (e = dmalloc(hook, &t->topk_local, sizeof(uint32_t) * 3 * gear::kTopkMaxGrid * gear::kTopkBins)) != hipSuccess ||
         (e = dmalloc(hook, &t->topk_keys, sizeof(uint64_t) * gear::kTopkMaxK)) != hipSuccess)
@@ -299,7 +299,7 @@ int create_table(const int64_t* elem_bytes, int32_t ncols, int64_t capacity, int
         (e = hipMemset(t->chunk_sums, 0, sizeof(uint64_t) * t->nchunks)) != hipSuccess ||
         (e = hipMemset(t->wg_min, 0xFF, sizeof(uint32_t) * gear::kSearchMaxGrid)) != hipSuccess ||
         (e = hipMemset(t->status, 0, sizeof(uint32_t))) != hipSuccess ||
-        (e = hipMemset(t->topk_hist, 0, sizeof(uint32_t) * 3 * gear::kTopkBins)) != hipSuccess ||
+        (e = hipMemset(t->topk_hist, 0, sizeof(uint32_t) * gear::kTopkHistRows * gear::kTopkBins)) != hipSuccess ||
         (e = hipMemset(t->topk_state, 0, sizeof(uint32_t) * gear::kTopkStateWords)) != hipSuccess ||
         (e = hipDeviceSynchronize()) != hipSuccess) {
         free_table(t);

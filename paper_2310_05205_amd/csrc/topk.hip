@@ -10,7 +10,8 @@
 // bits.  Its three 12-bit digits give small priorities their own pass-0
 // bins (every value below 256 is one bin) and spread skewed distributions
 // over many bins.  Selection stops early once the chosen bin is a single
-// value or is taken whole.  No workgroup waits for another and no kernel
+// value, is taken whole, or is small enough that all of it joins the ranked
+// keys and the ranking drops what lies past K.  No workgroup waits for another and no kernel
 // fences memory: workgroup 0 of each kernel stores the selection state it
 // derived, and the next kernel (after the kernel boundary that makes it and
 // the previous pass's complete histogram visible) derives at most one more
@@ -28,14 +29,16 @@
 //                       workgroup's count above and at it, hence this
 //                       workgroup's output offsets; one scan per batch of
 //                       loads orders its keys by slot.  It writes
-//                       (p << 32 | ~slot) of every slot above the threshold
-//                       and of the lowest-slot ones at it.
-//   topk_rank_emit_kernel  a key's place in descending order is the number
-//                       of larger keys (keys hold the slot, so they are
-//                       unique); every workgroup stages all K keys in LDS
-//                       and ranks 32 of them, 32 lanes per key, then writes
-//                       slot, window start and weight at each key's place
-//                       and clears the histograms for the next call.
+//                       the priority and the slot of every key above the
+//                       threshold and of the lowest-slot ones at it, each
+//                       group in slot order.
+//   topk_rank_emit_kernel  a key's place in descending order is the number of
+//                       larger priorities plus, as the list is in slot order
+//                       wherever priorities are equal, the number of equal
+//                       ones before it; every workgroup stages the priorities
+//                       in LDS and ranks 32 keys, four per wave, then writes
+//                       slot, window start and weight at each key's place and
+//                       clears the histograms for the next call.
 //
 // Loads that a derivation waits for are issued before the bulk priority
 // loads: vector loads complete in issue order, so the reverse would make the
@@ -70,6 +73,7 @@ struct TopkState {
     uint32_t total;   // number of slots with non-zero priority
     int32_t passes;   // digits chosen; keys are compared after >> (36 - 12 * passes)
     uint32_t flags;
+    uint32_t take;    // keys that are ranked: K, or up to ranked_most(K) when a small bin is taken whole
 };
 static_assert(sizeof(TopkState) * (kPasses + 1) <= kTopkStateWords * sizeof(uint32_t), "state buffer");
 
@@ -79,6 +83,14 @@ __device__ __forceinline__ uint64_t order_key(uint32_t p) {
     const int e = 31 - __clz(p | 1u);
     const uint32_t mant = (p << (31 - e)) & 0x7FFFFFFFu;
     return ((uint64_t)e << 31) | mant;
+}
+
+// The most keys that are ranked.  A whole bin of at most a quarter of K costs
+// less to rank than another pass over the priorities (200000 log-normal
+// priorities, K = 1000: 27.4 -> 21.8 us).
+__host__ __device__ __forceinline__ int ranked_most(int K) {
+    const int most = K + K / 4 + 256;
+    return most < kTopkMaxK ? most : kTopkMaxK;
 }
 
 __device__ __forceinline__ int state_shift(const TopkState& st) { return kKeyBits - kDigit * st.passes; }
@@ -128,9 +140,35 @@ __device__ __forceinline__ void load_batch(const uint32_t* __restrict__ prio, in
 // thread order is descending bin order; .w is the highest).
 __device__ __forceinline__ int first_bin() { return kBins - 4 - 4 * (int)threadIdx.x; }
 
+// The global histograms: one row each of passes 1 and 2, then `rows0` rows of
+// pass 0, which workgroups add into in turn.  With one row, the 256 workgroups
+// of a large table add into the same few hundred bins one after another (an
+// atomic on one address takes about 11 ns): pass 0 of 2^22 priorities was bound
+// by that.  Selects with 1 / 2 / 4 / 8 rows, K = 8192: Pareto 33.7 / 30.0 / 29.6 /
+// 29.7 us, log-normal 48.0 / 38.6 / 39.3 / 39.5.  Tables of less than
+// kRowsGrid workgroups use one row (5000 priorities: 18.0 us, 18.7 with four).
+constexpr int kRowsGrid = 16;
+__device__ __forceinline__ int hist_row(int pass, int rows0) {
+    return pass == 0 ? 2 + (int)blockIdx.x % rows0 : pass - 1;
+}
+
 // This thread's four bins of digit pass q's global histogram.
-__device__ __forceinline__ uint4 load_row(const uint32_t* __restrict__ hist, int q) {
-    return *reinterpret_cast<const uint4*>(hist + q * kBins + first_bin());
+__device__ __forceinline__ uint4 load_row(const uint32_t* __restrict__ hist, int q, int rows0) {
+    const uint32_t* at = hist + first_bin();
+    if (q > 0) return *reinterpret_cast<const uint4*>(at + (q - 1) * kBins);
+    uint4 h = *reinterpret_cast<const uint4*>(at + 2 * kBins);
+    if (rows0 == 1) return h;
+    uint4 more[kTopkRows0 - 1];
+#pragma unroll
+    for (int r = 1; r < kTopkRows0; r++) more[r - 1] = *reinterpret_cast<const uint4*>(at + (2 + r) * kBins);
+#pragma unroll
+    for (int r = 1; r < kTopkRows0; r++) {
+        h.x += more[r - 1].x;
+        h.y += more[r - 1].y;
+        h.z += more[r - 1].z;
+        h.w += more[r - 1].w;
+    }
+    return h;
 }
 
 struct DeriveShared {
@@ -177,7 +215,16 @@ __device__ TopkState derive_pass(uint4 h, int q, const TopkState& prev, uint32_t
         st.passes = q + 1;
         const int mant_bits = kDigit * (q + 1) - 5;  // mantissa bits the prefix fixes
         const int e = (int)(st.prefix >> mant_bits);
-        if (q + 1 == kPasses || bins[j] == st.k_rem || e <= mant_bits) st.flags |= kDone;
+        if (q + 1 == kPasses || bins[j] == st.k_rem || e <= mant_bits) {
+            st.flags |= kDone;
+        } else {
+            const uint64_t with_bin = (uint64_t)(K - prev.k_rem) + cum + bins[j];
+            if (with_bin <= (uint64_t)ranked_most((int)K)) {
+                st.k_rem = bins[j];
+                st.take = (uint32_t)with_bin;
+                st.flags |= kDone;
+            }
+        }
         sh.state[q] = st;
     }
     __syncthreads();
@@ -191,6 +238,7 @@ __device__ __forceinline__ TopkState initial_state(uint32_t K) {
     st.total = 0;
     st.passes = 0;
     st.flags = 0;
+    st.take = K;
     return st;
 }
 
@@ -204,8 +252,21 @@ __device__ TopkState state_after(int q, const TopkState& stored, uint4 row, uint
     return decided(s) ? s : derive_pass(row, q - 1, s, K, sh);
 }
 
+// The smallest priority p >= 1 whose order key is at least X, or 2^32 if
+// there is none.  Keys of the priorities with leading one at bit e are
+// (e << 31) | (r << (31 - e)) for p = 2^e + r, increasing in r.
+__device__ __forceinline__ uint64_t first_priority_with_key(uint64_t X) {
+    const uint64_t e = X >> 31;
+    if (e > 31) return 1ull << 32;
+    const uint64_t m = X & 0x7FFFFFFFull;
+    const int sh = 31 - (int)e;
+    const uint64_t r = (m + (1ull << sh) - 1) >> sh;
+    if (r < (1ull << e)) return (1ull << e) + r;
+    return 2ull << e;  // the first priority of the next leading-one position (2^32: none)
+}
+
 __global__ __launch_bounds__(kTopkThreads) void topk_hist_kernel(const uint32_t* __restrict__ prio, int64_t N,
-                                                                 int64_t chunk, int pass, uint32_t K,
+                                                                 int64_t chunk, int pass, uint32_t K, int rows0,
                                                                  uint32_t* __restrict__ hist,
                                                                  uint32_t* __restrict__ local,
                                                                  TopkState* __restrict__ states) {
@@ -214,7 +275,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_hist_kernel(const uint32_t*
     __shared__ uint64_t s_wt[kTopkWaves];
     TopkState prev = initial_state(K);
     if (pass > 0) {
-        const uint4 row = load_row(hist, pass - 1);
+        const uint4 row = load_row(hist, pass - 1, rows0);
         const TopkState stored = states[pass - 1];
         prev = state_after(pass, stored, row, K, dsh);
         if (blockIdx.x == 0 && threadIdx.x == 0) states[pass] = prev;  // for the next kernel
@@ -222,6 +283,11 @@ __global__ __launch_bounds__(kTopkThreads) void topk_hist_kernel(const uint32_t*
     if (decided(prev)) return;  // nothing left to histogram
     const int prev_shift = kKeyBits - kDigit * pass;
     const int shift = prev_shift - kDigit;
+    // Pass > 0: priorities [in_lo, in_lo + in_width) have the prefix; the bin
+    // is not empty, so both fit 32 bits, and 0 is never inside.
+    const uint64_t p_lo = first_priority_with_key(prev.prefix << prev_shift);
+    const uint32_t in_lo = (uint32_t)p_lo;
+    const uint32_t in_width = (uint32_t)(first_priority_with_key((prev.prefix + 1) << prev_shift) - p_lo);
     int64_t lo, hi;
     wg_range(N, chunk, lo, hi);
     uint32_t v[kVec][4];
@@ -249,16 +315,16 @@ __global__ __launch_bounds__(kTopkThreads) void topk_hist_kernel(const uint32_t*
                     atomicAdd(&copy[p != 0u ? d : pad], 1u);
                 }
             }
-        } else {
+            } else {
+            // The keys of the chosen prefix are the priorities of one range:
+            // one compare each, and the key only for those inside.
 #pragma unroll
             for (int k = 0; k < kVec; k++) {
 #pragma unroll
                 for (int q = 0; q < 4; q++) {
                     const uint32_t p = v[k][q];
-                    const uint64_t key = order_key(p);
-                    const bool counted = p != 0u && (key >> prev_shift) == prev.prefix;
-                    const uint32_t bin = (uint32_t)(key >> shift) & (uint32_t)(kBins - 1);
-                    if (counted) atomicAdd(&copy[bin], 1u);
+                    if (p - in_lo < in_width)
+                        atomicAdd(&copy[(uint32_t)(order_key(p) >> shift) & (uint32_t)(kBins - 1)], 1u);
                 }
             }
         }
@@ -276,7 +342,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_hist_kernel(const uint32_t*
         h.z += x.z;
         h.w += x.w;
     }
-    uint32_t* out = hist + pass * kBins + b0;
+    uint32_t* out = hist + hist_row(pass, rows0) * kBins + b0;
     if (h.x) atomicAdd(out + 0, h.x);
     if (h.y) atomicAdd(out + 1, h.y);
     if (h.z) atomicAdd(out + 2, h.z);
@@ -293,19 +359,6 @@ __global__ __launch_bounds__(kTopkThreads) void topk_hist_kernel(const uint32_t*
     S.y = S.z + h.y;
     S.x = S.y + h.x;
     *reinterpret_cast<uint4*>(local + ((size_t)pass * kTopkMaxGrid + blockIdx.x) * kBins + b0) = S;
-}
-
-// The smallest priority p >= 1 whose order key is at least X, or 2^32 if
-// there is none.  Keys of the priorities with leading one at bit e are
-// (e << 31) | (r << (31 - e)) for p = 2^e + r, increasing in r.
-__device__ __forceinline__ uint64_t first_priority_with_key(uint64_t X) {
-    const uint64_t e = X >> 31;
-    if (e > 31) return 1ull << 32;
-    const uint64_t m = X & 0x7FFFFFFFull;
-    const int sh = 31 - (int)e;
-    const uint64_t r = (m + (1ull << sh) - 1) >> sh;
-    if (r < (1ull << e)) return (1ull << e) + r;
-    return 2ull << e;  // the first priority of the next leading-one position (2^32: none)
 }
 
 // A decided state as a priority range: keys at the threshold are the
@@ -376,12 +429,13 @@ __global__ __launch_bounds__(kTopkThreads) void topk_compact_kernel(const uint32
                                                                     const uint32_t* __restrict__ hist,
                                                                     const uint32_t* __restrict__ local, int grid,
                                                                     TopkState* __restrict__ states,
-                                                                    uint64_t* __restrict__ keys) {
+                                                                    uint32_t* __restrict__ sel_p,
+                                                                    uint32_t* __restrict__ sel_slot) {
     __shared__ DeriveShared dsh;
     __shared__ uint32_t s_pre[kVec * kTopkWaves];  // per (load, wave): packed counts, then their prefix
     __shared__ uint64_t s_base[5];                 // above base, at base, total above, own above, own at
     __shared__ uint32_t s_batch;                   // packed counts of the whole batch
-    const uint4 row = load_row(hist, kPasses - 1);
+    const uint4 row = load_row(hist, kPasses - 1, 1);
     const TopkState stored = states[kPasses - 1];
     int64_t lo, hi;
     wg_range(N, chunk, lo, hi);
@@ -463,16 +517,23 @@ __global__ __launch_bounds__(kTopkThreads) void topk_compact_kernel(const uint32
             const int64_t e0 = base + ((int64_t)k * kTopkThreads + threadIdx.x) * 4;
 #pragma unroll
             for (int q = 0; q < 4; q++) {
-                const uint64_t key = ((uint64_t)v[k][q] << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)(e0 + q));
-                // The counts bound both positions by K; the checks keep a
-                // priority changed under a running selection from writing
-                // past the key buffer.
+                // The counts bound both positions by st.take; the checks keep
+                // a priority changed under a running selection from writing
+                // past the list.
+                const uint32_t slot = (uint32_t)(e0 + q);
                 if (cls[k] & (1u << q)) {
-                    if (og < (uint64_t)K) keys[og] = key;
+                    if (og < (uint64_t)st.take) {
+                        sel_p[og] = v[k][q];
+                        sel_slot[og] = slot;
+                    }
                     og++;
                 }
                 if (cls[k] & (16u << q)) {
-                    if (oe < e_need && total_gt + oe < (uint64_t)K) keys[total_gt + oe] = key;
+                    const uint64_t at = total_gt + oe;
+                    if (oe < e_need && at < (uint64_t)st.take) {
+                        sel_p[at] = v[k][q];
+                        sel_slot[at] = slot;
+                    }
                     oe++;
                 }
             }
@@ -486,120 +547,149 @@ __global__ __launch_bounds__(kTopkThreads) void topk_compact_kernel(const uint32
 static_assert(kVec * kTopkWaves == 64, "one lane of wave 0 per (load, wave) count");
 static_assert(kBatch < 65536, "a batch's counts fit the 16-bit fields");
 
-// Number of selected keys: K, or every candidate when there are fewer.
-__device__ __forceinline__ int selected(const TopkState& st, int32_t K) {
-    return (st.flags & kAll) ? (int)st.total : K;
-}
-
-// Rank and emit in one launch.  Keys are unique (they hold the slot), so a
-// key's place in descending order is the number of larger keys.  The
-// compaction wrote the n_gt keys above the threshold first, then those at
-// it, each group in slot order.  When every key at the threshold has the
-// same priority (the usual case: a threshold fixed to one value), a key at
-// it is preceded by all keys above and by the keys at it with lower slots,
-// so its place is its position in the list, and a key above the threshold
-// only needs comparing with the n_gt keys above it.  Otherwise every key is
-// compared with all n selected keys.
+// Rank and emit in one launch.  The list holds the n_gt keys above the
+// threshold, then those at it, each group in slot order, and a key above is
+// larger than any at it, so among equal priorities list order is slot order
+// throughout: key i comes after the larger priorities and the equal ones before
+// it.  A key at a threshold of one value is preceded by all keys above and the
+// earlier ones at it: its place is its position, and the keys above need
+// comparing only with each other.
 //
-// Every workgroup stages the keys to compare with in LDS (positions past
-// them read as 0, below every key, since p >= 1) and ranks kEmitKeys keys,
-// kEmitLanes lanes per key each counting the larger keys among every
-// kEmitLanes-th pair of the staged list.  The lanes of one key read
-// consecutive pairs and the two keys of a wave read the same pairs, so every
-// LDS read is a conflict-free broadcast.  The counts are summed within each
-// 32-lane half of a wave, and the half's last lane writes slot, window start
-// and weight at its key's place.  Workgroups also clear the digit histograms
-// for the next call.
-constexpr int kEmitThreads = 1024;
-constexpr int kEmitLanes = 32;
-constexpr int kEmitKeys = kEmitThreads / kEmitLanes;
-constexpr int kEmitPad = 2 * kEmitLanes;  // staged keys per compare round (one pair per lane)
-static_assert(kTopkMaxK % kEmitPad == 0, "a padded key count never passes the key buffer");
-constexpr int kEmitLoads = kTopkMaxK / 2 / kEmitThreads;  // 16-byte loads per thread for the largest K
+// Every workgroup stages the priorities to compare with in LDS (positions past
+// them read as 0, below every key, since p >= 1).  A wave ranks kEmitKeys keys:
+// its lanes read 256 staged priorities at a time, and one LDS read serves sixteen
+// 32-bit compares, each counted per lane (counting with ballots and scalar bit
+// counts was slower: two scalar instructions per compare).  In the 256 that hold
+// the wave's own keys a compare also looks at the position; before them an
+// equal priority counts (p > key - 1), behind them it does not.  Against 64-bit
+// compares of (priority, slot), two per LDS read: K = 16384 of 2^22 Pareto
+// priorities 51.1 -> 45.5 us, K = 8192 33.9 -> 33.7.
+constexpr int kEmitThreads = 512;
+constexpr int kEmitKeys = 4;                                    // per wave
+constexpr int kEmitGroup = kEmitThreads / 64 * kEmitKeys;       // per workgroup
+constexpr int kEmitChunk = 256;                                 // staged priorities per step of a wave
+static_assert(kTopkMaxK % kEmitChunk == 0 && kEmitChunk % kEmitKeys == 0, "a wave's keys lie in one chunk");
+constexpr int kEmitLoads = kTopkMaxK / 4 / kEmitThreads;        // 16-byte loads per thread for the longest list
 
-__device__ __forceinline__ ulonglong2 keep_below(ulonglong2 v, int e, int lim) {
-    return make_ulonglong2(2 * e < lim ? v.x : 0ull, 2 * e + 1 < lim ? v.y : 0ull);
+__device__ __forceinline__ uint4 keep_below(uint4 v, int e, int lim) {
+    return make_uint4(4 * e < lim ? v.x : 0u, 4 * e + 1 < lim ? v.y : 0u, 4 * e + 2 < lim ? v.z : 0u,
+                      4 * e + 3 < lim ? v.w : 0u);
 }
 
-__global__ __launch_bounds__(kEmitThreads) void topk_rank_emit_kernel(const uint64_t* __restrict__ keys,
+__device__ __forceinline__ void count_above(uint4 y, uint32_t t, uint32_t& l) {
+    l += (uint32_t)(y.x > t);
+    l += (uint32_t)(y.y > t);
+    l += (uint32_t)(y.z > t);
+    l += (uint32_t)(y.w > t);
+}
+
+__global__ __launch_bounds__(kEmitThreads) void topk_rank_emit_kernel(const uint32_t* __restrict__ sel_p,
+                                                                      const uint32_t* __restrict__ sel_slot,
                                                                       const TopkState* __restrict__ state, int32_t K,
                                                                       uint64_t span, uint64_t seed,
                                                                       int64_t* __restrict__ idx,
                                                                       int32_t* __restrict__ start,
                                                                       float* __restrict__ w, uint32_t* status,
-                                                                      uint32_t* __restrict__ hist) {
-    __shared__ ulonglong2 staged[kTopkMaxK / 2];
-    const int tid = (int)threadIdx.x;
-    const int pairs = (K + kEmitPad - 1) / kEmitPad * (kEmitPad / 2);  // within the kTopkMaxK-entry buffer
-    // The state, this thread's key and the first kEmitThreads pairs of the
-    // list are loaded together (one memory round trip), from indices
-    // clamped into the padded list.
-    const ulonglong2* kp = reinterpret_cast<const ulonglong2*>(keys);
-    const ulonglong2 v0 = kp[tid < pairs ? tid : pairs - 1];
-    const int i = blockIdx.x * kEmitKeys + tid / kEmitLanes;
-    const uint64_t km = keys[i < K ? i : K - 1];
+                                                                      int rows0, uint32_t* __restrict__ hist) {
+    __shared__ uint4 staged[kTopkMaxK / 4];
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int quads = (ranked_most(K) + 3) / 4;  // within the kTopkMaxK-entry list
+    // The state, this wave's keys and the first kEmitThreads quads of the list
+    // are loaded together (one memory round trip), from indices clamped into
+    // the list.
+    const uint4* list = reinterpret_cast<const uint4*>(sel_p);
+    const uint4 v0 = list[tid < quads ? tid : quads - 1];
+    const int i0 = (int)blockIdx.x * kEmitGroup + wave * kEmitKeys;
+    const int mine = i0 + (lane & (kEmitKeys - 1));  // the key that this lane emits, when lane < kEmitKeys
+    const int at = mine < kTopkMaxK ? mine : kTopkMaxK - 1;
+    const uint32_t my_p = sel_p[at], my_slot = sel_slot[at];
     const TopkState st = *state;
-    const int n = selected(st, K);
+    const bool all = (st.flags & kAll) != 0;
+    const int n = all ? (int)st.total : (int)st.take;  // keys in the list
+    int n_gt = all ? n : (int)st.take - (int)st.k_rem;  // keys above the threshold, at the front of the list
+    n_gt = n_gt < 0 ? 0 : (n_gt < n ? n_gt : n);
     uint64_t p_lo, p_hi;
     threshold_range(st, p_lo, p_hi);
-    const bool all = (st.flags & kAll) != 0;
-    int n_gt = all ? n : K - (int)st.k_rem;  // keys above the threshold, at the front of the list
-    n_gt = n_gt < 0 ? 0 : (n_gt < n ? n_gt : n);
     const bool one = !all && p_hi - p_lo == 1;  // every key at the threshold has priority p_lo
     const int lim = one ? n_gt : n;             // keys that some ranked key is compared with
-    const int pl = (lim + kEmitPad - 1) / kEmitPad * (kEmitPad / 2);  // staged pairs, <= pairs
-    if (tid < pl) staged[tid] = keep_below(v0, tid, lim);
-    if (pl > kEmitThreads) {  // the same branch for the whole workgroup
-        ulonglong2 v[kEmitLoads - 1];
+    const int chunks = (lim + kEmitChunk - 1) / kEmitChunk;
+    const int fill = chunks * (kEmitChunk / 4);  // staged quads
+    if (tid < fill) staged[tid] = keep_below(v0, tid, lim);
+    if (fill > kEmitThreads) {  // the same branch for the whole workgroup
+        uint4 v[kEmitLoads - 1];
 #pragma unroll
         for (int k = 1; k < kEmitLoads; k++) {
             const int e = k * kEmitThreads + tid;
-            v[k - 1] = kp[e < pl ? e : pl - 1];
+            v[k - 1] = list[e < quads ? e : quads - 1];
         }
 #pragma unroll
         for (int k = 1; k < kEmitLoads; k++) {
             const int e = k * kEmitThreads + tid;
-            if (e < pl) staged[e] = keep_below(v[k - 1], e, lim);
+            if (e < fill) staged[e] = keep_below(v[k - 1], e, lim);
         }
     }
-    for (int h = blockIdx.x * kEmitThreads + tid; h < kPasses * kBins; h += gridDim.x * kEmitThreads)
+    for (int h = (int)blockIdx.x * kEmitThreads + tid; h < (2 + rows0) * kBins; h += (int)gridDim.x * kEmitThreads)
         hist[h] = 0u;  // every digit pass of this call is done
     if (blockIdx.x == 0 && tid == 0 && (st.flags & kInconsistent)) atomicOr(status, GEAR_STATUS_INTERNAL);
     __syncthreads();
-    const int lane = tid & (kEmitLanes - 1);
-    const bool by_position = one && i >= n_gt;        // a key at a one-value threshold
-    const uint64_t mine = i < lim ? km : ~0ull;       // ~0: larger than every key, counts nothing
-    uint32_t c = 0;
-#pragma unroll 8
-    for (int q = lane; q < pl; q += kEmitLanes) {
-        const ulonglong2 y = staged[q];
-        c += (uint32_t)(y.x > mine) + (uint32_t)(y.y > mine);
+    uint32_t key[kEmitKeys];
+    int c[kEmitKeys];
+    uint32_t l[kEmitKeys] = {0, 0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < kEmitKeys; k++) {
+        key[k] = (uint32_t)__builtin_amdgcn_readlane((int)my_p, k);
+        if (i0 + k >= lim || key[k] == 0u) key[k] = 0xFFFFFFFFu;  // not ranked: nothing is larger
+        c[k] = 0;
     }
-    // Sum over the 32 lanes of this key: row scans, then row 0's total into
-    // row 1 and row 2's into row 3, so lanes 31 and 63 hold the two keys' sums.
-    c += dpp32<0x111, 0xf>(c);
-    c += dpp32<0x112, 0xf>(c);
-    c += dpp32<0x114, 0xf>(c);
-    c += dpp32<0x118, 0xf>(c);
-    c += dpp32<0x142, 0xa>(c);
-    if (lane != kEmitLanes - 1 || i >= K) return;
-    if (i < n) {
-        const uint32_t b = by_position ? (uint32_t)i : c;
-        if (b >= (uint32_t)n) {  // a key list changed under a running selection
+    if (i0 < lim) {
+        const int own = i0 / kEmitChunk;
+        for (int q = 0; q < own; q++) {
+            const uint4 y = staged[q * 64 + lane];
+#pragma unroll
+            for (int k = 0; k < kEmitKeys; k++) count_above(y, key[k] - 1, l[k]);
+        }
+        {
+            const uint4 y = staged[own * 64 + lane];
+            const int j = own * kEmitChunk + lane * 4;
+#pragma unroll
+            for (int k = 0; k < kEmitKeys; k++) {
+                const int i = i0 + k;
+                c[k] += __popcll(__ballot(y.x > key[k] - (j < i ? 1u : 0u))) +
+                        __popcll(__ballot(y.y > key[k] - (j + 1 < i ? 1u : 0u))) +
+                        __popcll(__ballot(y.z > key[k] - (j + 2 < i ? 1u : 0u))) +
+                        __popcll(__ballot(y.w > key[k] - (j + 3 < i ? 1u : 0u)));
+            }
+        }
+        for (int q = own + 1; q < chunks; q++) {
+            const uint4 y = staged[q * 64 + lane];
+#pragma unroll
+            for (int k = 0; k < kEmitKeys; k++) count_above(y, key[k], l[k]);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < kEmitKeys; k++) c[k] += __builtin_amdgcn_readlane((int)wave_inclusive_scan32(l[k]), 63);
+    if (lane >= kEmitKeys) return;
+    if (mine < n) {
+        const bool by_position = one && mine >= n_gt;  // a key at a one-value threshold
+        const int counted = lane == 0 ? c[0] : lane == 1 ? c[1] : lane == 2 ? c[2] : c[3];
+        const uint32_t b = by_position ? (uint32_t)mine : (uint32_t)counted;
+        if (b >= (uint32_t)n) {  // a list changed under a running selection
             atomicOr(status, GEAR_STATUS_INTERNAL);
             return;
         }
-        idx[b] = (int64_t)(0xFFFFFFFFu - (uint32_t)km);
+        if (b >= (uint32_t)K) return;  // of a bin taken whole, past the K-th
+        idx[b] = (int64_t)my_slot;
         start[b] = (int32_t)scale_draw(splitmix64_out(seed, 2 * (uint64_t)b + 1), span);
         if (w) w[b] = 1.0f;
-    } else {
-        idx[i] = -1;
-        start[i] = 0;
-        if (w) w[i] = 0.0f;
-        if (i == n) atomicOr(status, GEAR_STATUS_NO_WEIGHT);
+    } else if (mine < K) {
+        idx[mine] = -1;
+        start[mine] = 0;
+        if (w) w[mine] = 0.0f;
+        if (mine == n) atomicOr(status, GEAR_STATUS_NO_WEIGHT);
     }
 }
-static_assert(kEmitLanes == 32 && kEmitThreads % 64 == 0, "the count sum covers the two halves of a wave");
+static_assert(kEmitKeys == 4, "counts are picked per lane");
 
 }  // namespace
 
@@ -615,17 +705,21 @@ hipError_t launch_topk(Table& t, int32_t K, int32_t L, uint64_t seed, int64_t* i
     // (digit pass q, or the compaction for q = kPasses) for the kernels after it.
     TopkState* states = reinterpret_cast<TopkState*>(t.topk_state);
     TopkState* state = states + kPasses;
+    const int rows0 = grid >= kRowsGrid ? kTopkRows0 : 1;
     hipError_t e;
     for (int pass = 0; pass < kPasses; pass++) {
         hipLaunchKernelGGL(topk_hist_kernel, dim3(grid), dim3(kTopkThreads), 0, s, t.priority, t.N, chunk, pass,
-                           (uint32_t)K, t.topk_hist, t.topk_local, states);
+                           (uint32_t)K, rows0, t.topk_hist, t.topk_local, states);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
+    uint32_t* sel_p = reinterpret_cast<uint32_t*>(t.topk_keys);
+    uint32_t* sel_slot = sel_p + kTopkMaxK;
     hipLaunchKernelGGL(topk_compact_kernel, dim3(grid), dim3(kTopkThreads), 0, s, t.priority, t.N, chunk,
-                       (uint32_t)K, t.topk_hist, t.topk_local, grid, states, t.topk_keys);
+                       (uint32_t)K, t.topk_hist, t.topk_local, grid, states, sel_p, sel_slot);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(topk_rank_emit_kernel, dim3((K + kEmitKeys - 1) / kEmitKeys), dim3(kEmitThreads), 0, s,
-                       t.topk_keys, state, K, (uint64_t)(t.T - L + 1), seed, idx, start, w, t.status, t.topk_hist);
+    hipLaunchKernelGGL(topk_rank_emit_kernel, dim3((ranked_most(K) + kEmitGroup - 1) / kEmitGroup), dim3(kEmitThreads),
+                       0, s, sel_p, sel_slot, state, K, (uint64_t)(t.T - L + 1), seed, idx, start, w, t.status,
+                       rows0, t.topk_hist);
     return hipGetLastError();
 }
 
