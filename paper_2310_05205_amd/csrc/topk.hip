@@ -424,6 +424,86 @@ __device__ __forceinline__ void wg_counts(const uint32_t* __restrict__ local, co
     }
 }
 
+// Where a compaction puts its keys: those of p_hi and above from the list's
+// start, the first e_need of [p_lo, p_hi) behind the total_gt above, in slot
+// order.
+struct Compaction {
+    uint64_t p_hi, p_lo, p_width;
+    uint64_t e_need, total_gt;
+    uint32_t limit;  // length of the list
+    uint32_t* sel_p;
+    uint32_t* sel_slot;
+};
+
+// One batch of a workgroup's keys; run_gt and run_eq are the keys above and at
+// the threshold before it and advance past it.
+__device__ __forceinline__ void compact_batch(const uint32_t v[kVec][4], int64_t base, const Compaction& to,
+                                              uint64_t& run_gt, uint64_t& run_eq, uint32_t* s_pre,
+                                              uint32_t& s_batch) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // Counts packed as above | at << 16: a batch holds at most kBatch keys.
+    uint32_t c[kVec], incl[kVec];
+    uint32_t cls[kVec];  // per element: bit q above, bit 4 + q at
+#pragma unroll
+    for (int k = 0; k < kVec; k++) {
+        c[k] = 0;
+        cls[k] = 0;
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const uint64_t p = v[k][q];
+            const bool gt = p >= to.p_hi;
+            const bool eq = p - to.p_lo < to.p_width;
+            c[k] += (uint32_t)gt | ((uint32_t)eq << 16);
+            cls[k] |= (gt ? 1u << q : 0u) | (eq ? 16u << q : 0u);
+        }
+        incl[k] = wave_inclusive_scan32(c[k]);
+        if (lane == 63) s_pre[k * kTopkWaves + wave] = incl[k];
+    }
+    __syncthreads();
+    if (wave == 0) {
+        // Exclusive scan of the kVec x kTopkWaves wave counts in (load, wave) order.
+        const uint32_t a = s_pre[lane];
+        const uint32_t s = wave_inclusive_scan32(a);
+        s_pre[lane] = s - a;
+        if (lane == 63) s_batch = s;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kVec; k++) {
+        if (cls[k] == 0) continue;
+        const uint32_t off = s_pre[k * kTopkWaves + wave] + incl[k] - c[k];
+        uint64_t og = run_gt + (off & 0xFFFFu);  // output position of this lane's first key above
+        uint64_t oe = run_eq + (off >> 16);      // slot-order rank of its first key at the threshold
+        const int64_t e0 = base + ((int64_t)k * kTopkThreads + threadIdx.x) * 4;
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            // The counts bound both positions by to.limit; the checks keep
+            // a priority changed under a running selection from writing
+            // past the list.
+            const uint32_t slot = (uint32_t)(e0 + q);
+            if (cls[k] & (1u << q)) {
+                if (og < (uint64_t)to.limit) {
+                    to.sel_p[og] = v[k][q];
+                    to.sel_slot[og] = slot;
+                }
+                og++;
+            }
+            if (cls[k] & (16u << q)) {
+                const uint64_t at = to.total_gt + oe;
+                if (oe < to.e_need && at < (uint64_t)to.limit) {
+                    to.sel_p[at] = v[k][q];
+                    to.sel_slot[at] = slot;
+                }
+                oe++;
+            }
+        }
+    }
+    const uint32_t tb = s_batch;
+    run_gt += tb & 0xFFFFu;
+    run_eq += tb >> 16;
+    __syncthreads();  // s_pre and s_batch are rewritten by the next batch
+}
+
 __global__ __launch_bounds__(kTopkThreads) void topk_compact_kernel(const uint32_t* __restrict__ prio, int64_t N,
                                                                     int64_t chunk, uint32_t K,
                                                                     const uint32_t* __restrict__ hist,
@@ -479,73 +559,69 @@ __global__ __launch_bounds__(kTopkThreads) void topk_compact_kernel(const uint32
     const uint64_t total_gt = s_base[2];
     uint64_t run_gt = s_base[0], run_eq = s_base[1];
     if (s_base[3] == 0 && (s_base[4] == 0 || run_eq >= e_need)) return;
+    const Compaction to{p_hi, p_lo, p_width, e_need, total_gt, st.take, sel_p, sel_slot};
     for (int64_t base = lo; base < hi; base += kBatch) {
         if (base != lo) load_batch(prio, base, hi, v);
-        // Counts packed as above | at << 16: a batch holds at most kBatch keys.
-        uint32_t c[kVec], incl[kVec];
-        uint32_t cls[kVec];  // per element: bit q above, bit 4 + q at
-#pragma unroll
-        for (int k = 0; k < kVec; k++) {
-            c[k] = 0;
-            cls[k] = 0;
-#pragma unroll
-            for (int q = 0; q < 4; q++) {
-                const uint64_t p = v[k][q];
-                const bool gt = p >= p_hi;
-                const bool eq = p - p_lo < p_width;
-                c[k] += (uint32_t)gt | ((uint32_t)eq << 16);
-                cls[k] |= (gt ? 1u << q : 0u) | (eq ? 16u << q : 0u);
-            }
-            incl[k] = wave_inclusive_scan32(c[k]);
-            if (lane == 63) s_pre[k * kTopkWaves + wave] = incl[k];
-        }
-        __syncthreads();
-        if (wave == 0) {
-            // Exclusive scan of the kVec x kTopkWaves wave counts in (load, wave) order.
-            const uint32_t a = s_pre[lane];
-            const uint32_t s = wave_inclusive_scan32(a);
-            s_pre[lane] = s - a;
-            if (lane == 63) s_batch = s;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kVec; k++) {
-            if (cls[k] == 0) continue;
-            const uint32_t off = s_pre[k * kTopkWaves + wave] + incl[k] - c[k];
-            uint64_t og = run_gt + (off & 0xFFFFu);  // output position of this lane's first key above
-            uint64_t oe = run_eq + (off >> 16);      // slot-order rank of its first key at the threshold
-            const int64_t e0 = base + ((int64_t)k * kTopkThreads + threadIdx.x) * 4;
-#pragma unroll
-            for (int q = 0; q < 4; q++) {
-                // The counts bound both positions by st.take; the checks keep
-                // a priority changed under a running selection from writing
-                // past the list.
-                const uint32_t slot = (uint32_t)(e0 + q);
-                if (cls[k] & (1u << q)) {
-                    if (og < (uint64_t)st.take) {
-                        sel_p[og] = v[k][q];
-                        sel_slot[og] = slot;
-                    }
-                    og++;
-                }
-                if (cls[k] & (16u << q)) {
-                    const uint64_t at = total_gt + oe;
-                    if (oe < e_need && at < (uint64_t)st.take) {
-                        sel_p[at] = v[k][q];
-                        sel_slot[at] = slot;
-                    }
-                    oe++;
-                }
-            }
-        }
-        const uint32_t tb = s_batch;
-        run_gt += tb & 0xFFFFu;
-        run_eq += tb >> 16;
-        __syncthreads();  // s_pre and s_batch are rewritten by the next batch
+        compact_batch(v, base, to, run_gt, run_eq, s_pre, s_batch);
     }
 }
 static_assert(kVec * kTopkWaves == 64, "one lane of wave 0 per (load, wave) count");
 static_assert(kBatch < 65536, "a batch's counts fit the 16-bit fields");
+
+// Tables of one batch: one workgroup keeps all priorities in registers and does
+// every digit pass and the compaction, so that a select is two launches instead
+// of five (K = 300 of 5000 priorities 18.0 -> 11.2 us).
+__global__ __launch_bounds__(kTopkThreads) void topk_small_kernel(const uint32_t* __restrict__ prio, int64_t N,
+                                                                  uint32_t K, TopkState* __restrict__ state,
+                                                                  uint32_t* __restrict__ sel_p,
+                                                                  uint32_t* __restrict__ sel_slot) {
+    __shared__ __align__(16) uint32_t sh[kLdsCopies * kLdsStride];
+    __shared__ DeriveShared dsh;
+    __shared__ uint32_t s_pre[kVec * kTopkWaves];
+    __shared__ uint32_t s_batch;
+    uint32_t v[kVec][4];
+    load_batch(prio, 0, N, v);
+    uint32_t* const copy = sh + (threadIdx.x % kLdsCopies) * kLdsStride;
+    const int b0 = first_bin();
+    TopkState st = initial_state(K);
+#pragma unroll 1
+    for (int pass = 0; pass < kPasses && !decided(st); pass++) {  // decided by the whole workgroup alike
+        for (int b = threadIdx.x * 4; b < kLdsCopies * kLdsStride; b += kTopkThreads * 4)
+            *reinterpret_cast<uint4*>(&sh[b]) = make_uint4(0u, 0u, 0u, 0u);
+        // Keys of the prefix so far: in pass 0 every non-zero priority.
+        const int prev_shift = kKeyBits - kDigit * pass;
+        const uint64_t p_lo = pass == 0 ? 1 : first_priority_with_key(st.prefix << prev_shift);
+        const uint64_t p_hi = pass == 0 ? 1ull << 32 : first_priority_with_key((st.prefix + 1) << prev_shift);
+        const uint32_t in_lo = (uint32_t)p_lo, in_width = (uint32_t)(p_hi - p_lo);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kVec; k++)
+#pragma unroll
+            for (int q = 0; q < 4; q++)
+                if (v[k][q] - in_lo < in_width)
+                    atomicAdd(&copy[(uint32_t)(order_key(v[k][q]) >> (prev_shift - kDigit)) & (uint32_t)(kBins - 1)], 1u);
+        __syncthreads();
+        uint4 h = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+        for (int c = 0; c < kLdsCopies; c++) {
+            const uint4 x = *reinterpret_cast<const uint4*>(&sh[c * kLdsStride + b0]);
+            h.x += x.x;
+            h.y += x.y;
+            h.z += x.z;
+            h.w += x.w;
+        }
+        st = derive_pass(h, pass, st, K, dsh);  // its barriers end the reads of `sh`
+    }
+    if (threadIdx.x == 0) *state = st;
+    uint64_t p_lo, p_hi;
+    threshold_range(st, p_lo, p_hi);
+    const bool all = (st.flags & kAll) != 0;
+    const uint64_t e_need = all ? 0 : st.k_rem;
+    const uint64_t n_gt = all ? st.total : st.take - st.k_rem;
+    const Compaction to{p_hi, p_lo, p_hi - p_lo, e_need, n_gt, st.take, sel_p, sel_slot};
+    uint64_t run_gt = 0, run_eq = 0;
+    compact_batch(v, 0, to, run_gt, run_eq, s_pre, s_batch);
+}
 
 // Rank and emit in one launch.  The list holds the n_gt keys above the
 // threshold, then those at it, each group in slot order, and a key above is
@@ -695,6 +771,21 @@ static_assert(kEmitKeys == 4, "counts are picked per lane");
 
 hipError_t launch_topk(Table& t, int32_t K, int32_t L, uint64_t seed, int64_t* idx, int32_t* start, float* w,
                        hipStream_t s) {
+    TopkState* states = reinterpret_cast<TopkState*>(t.topk_state);
+    uint32_t* sel_p = reinterpret_cast<uint32_t*>(t.topk_keys);
+    uint32_t* sel_slot = sel_p + kTopkMaxK;
+    const dim3 rank_grid((ranked_most(K) + kEmitGroup - 1) / kEmitGroup);
+    if (t.N <= kBatch) {
+        hipLaunchKernelGGL(topk_small_kernel, dim3(1), dim3(kTopkThreads), 0, s, t.priority, t.N, (uint32_t)K,
+                           states + kPasses, sel_p, sel_slot);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        // The digit histograms were not used: -2 rows, none to clear.
+        hipLaunchKernelGGL(topk_rank_emit_kernel, rank_grid, dim3(kEmitThreads), 0, s, sel_p, sel_slot,
+                           states + kPasses, K, (uint64_t)(t.T - L + 1), seed, idx, start, w, t.status, -2,
+                           t.topk_hist);
+        return hipGetLastError();
+    }
     // chunk: a multiple of 4 * kTopkThreads (aligned 16-byte loads).
     const int64_t unit = 4 * kTopkThreads;
     int64_t g = (t.N + unit - 1) / unit;
@@ -703,7 +794,6 @@ hipError_t launch_topk(Table& t, int32_t K, int32_t L, uint64_t seed, int64_t* i
     const int grid = (int)((t.N + chunk - 1) / chunk);
     // states[q]: the state after digit passes 0 .. q-1, stored by kernel q
     // (digit pass q, or the compaction for q = kPasses) for the kernels after it.
-    TopkState* states = reinterpret_cast<TopkState*>(t.topk_state);
     TopkState* state = states + kPasses;
     const int rows0 = grid >= kRowsGrid ? kTopkRows0 : 1;
     hipError_t e;
@@ -712,13 +802,10 @@ hipError_t launch_topk(Table& t, int32_t K, int32_t L, uint64_t seed, int64_t* i
                            (uint32_t)K, rows0, t.topk_hist, t.topk_local, states);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    uint32_t* sel_p = reinterpret_cast<uint32_t*>(t.topk_keys);
-    uint32_t* sel_slot = sel_p + kTopkMaxK;
     hipLaunchKernelGGL(topk_compact_kernel, dim3(grid), dim3(kTopkThreads), 0, s, t.priority, t.N, chunk,
                        (uint32_t)K, t.topk_hist, t.topk_local, grid, states, sel_p, sel_slot);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(topk_rank_emit_kernel, dim3((ranked_most(K) + kEmitGroup - 1) / kEmitGroup), dim3(kEmitThreads),
-                       0, s, sel_p, sel_slot, state, K, (uint64_t)(t.T - L + 1), seed, idx, start, w, t.status,
+    hipLaunchKernelGGL(topk_rank_emit_kernel, rank_grid, dim3(kEmitThreads), 0, s, sel_p, sel_slot, state, K, (uint64_t)(t.T - L + 1), seed, idx, start, w, t.status,
                        rows0, t.topk_hist);
     return hipGetLastError();
 }
