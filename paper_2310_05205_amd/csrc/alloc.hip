@@ -334,6 +334,28 @@ Source source_kind(const void* p, int device) {
     return a.type == hipMemoryTypeHost ? Source::kPinned : Source::kOther;
 }
 
+bool in_one_allocation(const void* p, int64_t bytes) {
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    const uintptr_t at = reinterpret_cast<uintptr_t>(p) - reinterpret_cast<uintptr_t>(base);
+    return at <= size && (uint64_t)bytes <= size - at;
+}
+
+bool meets_table(const Table& t, const void* p, int64_t bytes) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(p);
+    const auto meets = [&](const void* base, int64_t size) {
+        const uintptr_t b = reinterpret_cast<uintptr_t>(base);
+        return a < b + (uintptr_t)size && b < a + (uintptr_t)bytes;
+    };
+    for (int c = 0; c < t.ncols; c++)
+        if (meets(t.col_dev[c], t.N * t.T * t.elem_bytes[c])) return true;
+    return meets(t.priority, t.N * (int64_t)sizeof(uint32_t));
+}
+
 hipError_t acquire_slot(Table& t, PinSlot& ps) {
     ps.k = t.pin_next;
     t.pin_next = (ps.k + 1) % kStageSlots;
@@ -423,7 +445,12 @@ int write_rows(Table& t, int64_t n, const int64_t* idx, const void* const* col_s
     if (!any_kernel) return GEAR_OK;
     SlotList list;
     int runs = 0;
-    if (find_runs(idx, n, true, list, runs)) {
+    // Rows of the table itself are written column by column: in one launch a
+    // column's rows could be replaced before another column has read them.
+    bool one_launch = find_runs(idx, n, true, list, runs);
+    for (int c = 0; c < t.ncols && one_launch; c++)
+        one_launch = !kernel_path[(size_t)c] || !meets_table(t, col_src[c], n * t.T * t.elem_bytes[c]);
+    if (one_launch) {
         Segment seg[GEAR_MAX_COLUMNS * kMaxRuns];
         int count = 0;
         for (int c = 0; c < t.ncols; c++) {

@@ -188,6 +188,10 @@ hipError_t launch_segments(const Segment* seg, int n, const WordTail* tail, hipS
 // or anything else (managed memory, another device).
 enum class Source { kDevice, kPinned, kPageable, kOther };
 Source source_kind(const void* p, int device);
+// Whether bytes [p, p + bytes) lie in one allocation that the runtime knows.
+bool in_one_allocation(const void* p, int64_t bytes);
+// Whether bytes [p, p + bytes) meet a column of the table or its priorities.
+bool meets_table(const Table& t, const void* p, int64_t bytes);
 // One slot of the pinned staging ring: a host list is copied into it by the CPU
 // and read in place by the kernels of one chunk.  A slot is refilled only
 // after the event recorded behind its last reader, so the host waits only when

@@ -349,8 +349,11 @@ extern "C" int gear_insert(gear_table* h, int64_t n, const void* const* col_src,
     // Rows in the table's own device memory go into an HBM table by one launch
     // for all columns and the priorities (host lists through a staging slot):
     // a copy or two per column and their gaps took 17.1 us for 77 rows of 100 KB
-    // in four columns, the one launch 8.3; 3 rows of 5 KB 16.5 and 7.5.  Rows on the host or another device, and
-    // tables on the host, take the copy engine's path.
+    // in four columns, the one launch 8.3; 3 rows of 5 KB 16.5 and 7.5.  Rows on
+    // the host or another device, and tables on the host, take the copy engine's
+    // path; so do sources that meet the table's own memory, where the order of
+    // the copies counts, and sources longer than their allocation, which a copy
+    // refuses and a kernel would read past.
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     bool one_launch = t->residency == GEAR_DEVICE && rows <= gear::kStageRows;
     // A captured insertion keeps the copies: staging slots belong to one run.
@@ -358,10 +361,17 @@ extern "C" int gear_insert(gear_table* h, int64_t n, const void* const* col_src,
         (void)hipGetLastError();
         one_launch = false;
     }
-    for (int c = 0; c < t->ncols && one_launch; c++)
-        one_launch = gear::source_kind(col_src[c], t->device) == gear::Source::kDevice;
-    const gear::Source prio_kind =
+    for (int c = 0; c < t->ncols && one_launch; c++) {
+        const int64_t bytes = n * t->T * t->elem_bytes[c];
+        one_launch = gear::source_kind(col_src[c], t->device) == gear::Source::kDevice &&
+                     gear::in_one_allocation(col_src[c], bytes) && !gear::meets_table(*t, col_src[c], bytes);
+    }
+    gear::Source prio_kind =
         one_launch ? gear::source_kind(priorities + skip, t->device) : gear::Source::kOther;
+    if ((prio_kind == gear::Source::kDevice || prio_kind == gear::Source::kPinned) &&
+        (!gear::in_one_allocation(priorities + skip, rows * (int64_t)sizeof(uint32_t)) ||
+         gear::meets_table(*t, priorities + skip, rows * (int64_t)sizeof(uint32_t))))
+        prio_kind = gear::Source::kOther;
     if (prio_kind != gear::Source::kOther) {
         const uint32_t* p = priorities + skip;
         // Short host lists travel in the kernel's arguments: reading them from a

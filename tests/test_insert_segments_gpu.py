@@ -108,3 +108,44 @@ def test_columns_on_the_host_or_mixed_take_the_copies():
         np.testing.assert_array_equal(t.priorities(), [9, 9, 9, 9, 5, 6, 7, 8, 9, 10])
     finally:
         t.close()
+
+
+def test_rows_of_the_table_itself_keep_the_order_of_the_copies():
+    """Sources in the table's own columns and priorities, not next to their
+    destinations: the first part of a wrapped batch is written before the second,
+    and a column before the next one."""
+    N, E = 4096, 64
+    rng = np.random.default_rng(3)
+    t = gear.Table([E, E], N, 1)
+    try:
+        rows = [rng.integers(0, 256, (N, E), dtype=np.uint8) for _ in range(2)]
+        p = rng.integers(1, 1000, N).astype(np.uint32)
+        t.insert(rows, p)
+        t.insert([r[:N - 1000] for r in rows], p[:N - 1000])  # the next batch wraps after 1000 rows
+        n = 2000
+        views = [t.column_view(c).view(N, E)[:n] for c in range(2)]
+        t.insert(views, np.full(n, 5, np.uint32))
+        for m in rows:
+            m[N - 1000:] = m[:1000].copy()
+            m[:1000] = m[1000:2000].copy()
+        for c in range(2):
+            np.testing.assert_array_equal(host(t.column_view(c)).reshape(N, E), rows[c])
+    finally:
+        t.close()
+
+
+def test_managed_rows_of_another_column():
+    """Column 1 takes the rows that the same call has written to column 0."""
+    N, E = 4096, 64
+    rng = np.random.default_rng(4)
+    t = gear.Table([E, E], N, 1)
+    try:
+        t.use_allocator(gear.GEAR_FIFO)
+        idx = t.allocate(N)
+        new = rng.integers(0, 256, (N, E), dtype=np.uint8)
+        t.write_rows(idx, [torch.from_numpy(new).to(cuda()), t.column_view(0)])
+        got = [host(t.column_view(c)).reshape(N, E) for c in range(2)]
+        np.testing.assert_array_equal(got[0][idx], new)
+        np.testing.assert_array_equal(got[1][idx], got[0])
+    finally:
+        t.close()

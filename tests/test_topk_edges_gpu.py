@@ -31,7 +31,7 @@ def _priorities(kind, N, rng):
 
 
 @pytest.mark.parametrize("kind", ["distinct", "narrow", "ties", "two bins", "sparse"])
-@pytest.mark.parametrize("N", [17, 4096, 20001, 70000])
+@pytest.mark.parametrize("N", [17, 4096, 16383, 16384, 16385, 20001, 70000])
 def test_topk_edges(N, kind):
     rng = np.random.default_rng(N)
     p = _priorities(kind, N, rng)
