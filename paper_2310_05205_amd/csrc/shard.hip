@@ -80,9 +80,9 @@ __device__ __forceinline__ bool before(uint32_t pa, int64_t ia, uint32_t pb, int
 // candidate are filled by further workgroups of the same launch.
 //
 // The kernel is a chain of memory round trips: the keys, three probe rounds
-// (16 lanes took four), the bracket, the results.  8 lists of 8192 took 15.2 us with 64-entry tiles,
-// 16 probe lanes, no early end and a fill launch of its own; now 9.2 (16 lists of
-// 16384: 56.8 -> 16.4).
+// (16 lanes took four), the bracket, the results.  8 lists of 8192 took 15.2 us
+// with 64-entry tiles, 16 probe lanes, no early end and a fill launch of its own;
+// now 9.2 (16 lists of 16384: 56.8 -> 16.4).
 constexpr int kMergeThreads = 512;
 constexpr int kMergeParts = 4;                          // threads per tile entry
 constexpr int kMergeTile = kMergeThreads / kMergeParts;  // 128 entries

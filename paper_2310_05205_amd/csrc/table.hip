@@ -349,7 +349,7 @@ extern "C" int gear_insert(gear_table* h, int64_t n, const void* const* col_src,
     // Rows in the table's own device memory go into an HBM table by one launch
     // for all columns and the priorities (host lists through a staging slot):
     // a copy or two per column and their gaps took 17.1 us for 77 rows of 100 KB
-    // in four columns, the one launch 8.3; 3 rows of 5 KB 16.5 and 7.5.  Rows on
+    // in four columns, the one launch 7.9; 3 rows of 5 KB 16.5 and 7.5.  Rows on
     // the host or another device, and tables on the host, take the copy engine's
     // path; so do sources that meet the table's own memory, where the order of
     // the copies counts, and sources longer than their allocation, which a copy

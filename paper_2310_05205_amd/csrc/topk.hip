@@ -11,11 +11,11 @@
 // bins (every value below 256 is one bin) and spread skewed distributions
 // over many bins.  Selection stops early once the chosen bin is a single
 // value, is taken whole, or is small enough that all of it joins the ranked
-// keys and the ranking drops what lies past K.  No workgroup waits for another and no kernel
-// fences memory: workgroup 0 of each kernel stores the selection state it
-// derived, and the next kernel (after the kernel boundary that makes it and
-// the previous pass's complete histogram visible) derives at most one more
-// digit from that histogram.
+// keys and the ranking drops what lies past K.  No workgroup waits for another
+// and no kernel fences memory: workgroup 0 of each kernel stores the selection
+// state it derived, and the next kernel (after the kernel boundary that makes
+// it and the previous pass's complete histogram visible) derives at most one
+// more digit from that histogram.
 //
 //   topk_hist_kernel    (x3) a workgroup histograms one digit of the keys
 //                       whose higher digits match the ones chosen so far,
@@ -805,7 +805,8 @@ hipError_t launch_topk(Table& t, int32_t K, int32_t L, uint64_t seed, int64_t* i
     hipLaunchKernelGGL(topk_compact_kernel, dim3(grid), dim3(kTopkThreads), 0, s, t.priority, t.N, chunk,
                        (uint32_t)K, t.topk_hist, t.topk_local, grid, states, sel_p, sel_slot);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(topk_rank_emit_kernel, rank_grid, dim3(kEmitThreads), 0, s, sel_p, sel_slot, state, K, (uint64_t)(t.T - L + 1), seed, idx, start, w, t.status,
+    hipLaunchKernelGGL(topk_rank_emit_kernel, rank_grid, dim3(kEmitThreads), 0, s, sel_p, sel_slot, state, K,
+                       (uint64_t)(t.T - L + 1), seed, idx, start, w, t.status,
                        rows0, t.topk_hist);
     return hipGetLastError();
 }
