@@ -208,18 +208,23 @@ constexpr int64_t row_piece() { return (int64_t)kRowThreads * row_unroll<V>(); }
 
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 
+// A row is pieces_per_row pieces, the last one of `last` elements.  Which piece this
+// is and its length are 32-bit: of a 64-bit `row_elems - off < P ? row_elems - off : P`
+// (no scalar compare, so a vector one) the compiler formed a scalar select for the
+// 4-byte elements that read a condition nothing had set, so the last piece of a
+// row was copied whole, into the next row.
 template <typename V>
 __global__ __launch_bounds__(kRowThreads) void scatter_rows_kernel(const int64_t* __restrict__ idx,
                                                                    const V* __restrict__ src, V* __restrict__ dst,
-                                                                   int64_t row_elems, int64_t pieces_per_row) {
+                                                                   int64_t row_elems, uint32_t pieces_per_row,
+                                                                   uint32_t last) {
     constexpr int U = row_unroll<V>();
     constexpr int64_t P = row_piece<V>();
-    const int64_t q = blockIdx.x;
-    const int64_t r = q / pieces_per_row;
-    const int64_t off = (q - r * pieces_per_row) * P;
-    const int64_t len = row_elems - off < P ? row_elems - off : P;
-    const V* s = src + r * row_elems + off;
-    V* d = dst + idx[r] * row_elems + off;
+    const uint32_t r = blockIdx.x / pieces_per_row;
+    const uint32_t piece = blockIdx.x - r * pieces_per_row;
+    const uint32_t len = piece + 1 < pieces_per_row ? (uint32_t)P : last;
+    const V* s = src + r * row_elems + piece * P;
+    V* d = dst + idx[r] * row_elems + piece * P;
     if (len == P) {
         V v[U];
 #pragma unroll
@@ -227,7 +232,7 @@ __global__ __launch_bounds__(kRowThreads) void scatter_rows_kernel(const int64_t
 #pragma unroll
         for (int k = 0; k < U; k++) __builtin_nontemporal_store(v[k], d + threadIdx.x + k * kRowThreads);
     } else {
-        for (int64_t e = threadIdx.x; e < len; e += kRowThreads)
+        for (uint32_t e = threadIdx.x; e < len; e += kRowThreads)
             __builtin_nontemporal_store(__builtin_nontemporal_load(s + e), d + e);
     }
 }
@@ -272,10 +277,12 @@ hipError_t launch_rows(const int64_t* d_idx, int64_t n, const uint8_t* src, uint
     // exceeds 2^31 - 1 workgroups.
     const int64_t ppr = (row_elems + P - 1) / P;
     const int64_t rows_per_launch = ppr >= 0x7FFFFFFF ? 1 : 0x7FFFFFFF / ppr;
+    const uint32_t last = (uint32_t)(row_elems - (ppr - 1) * P);
     for (int64_t r0 = 0; r0 < n; r0 += rows_per_launch) {
         const int64_t m = n - r0 < rows_per_launch ? n - r0 : rows_per_launch;
         hipLaunchKernelGGL(scatter_rows_kernel<V>, dim3((unsigned)(m * ppr)), dim3(kRowThreads), 0, s, d_idx + r0,
-                           reinterpret_cast<const V*>(src + r0 * row_bytes), reinterpret_cast<V*>(dst), row_elems, ppr);
+                           reinterpret_cast<const V*>(src + r0 * row_bytes), reinterpret_cast<V*>(dst), row_elems,
+                           (uint32_t)ppr, last);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
