@@ -262,7 +262,7 @@ __global__ __launch_bounds__(kRowThreads) void scatter_small_rows_kernel(const i
 
 template <typename V>
 hipError_t launch_rows(const int64_t* d_idx, int64_t n, const uint8_t* src, uint8_t* dst, int64_t row_bytes,
-                       hipStream_t s) {
+                       int64_t most, hipStream_t s) {
     constexpr int64_t P = row_piece<V>();
     const int64_t row_elems = row_bytes / (int64_t)sizeof(V);
     if (row_elems * 2 < P) {
@@ -273,10 +273,10 @@ hipError_t launch_rows(const int64_t* d_idx, int64_t n, const uint8_t* src, uint
                            magic);
         return hipGetLastError();
     }
-    // One workgroup per piece; rows are split over launches so that no grid
-    // exceeds 2^31 - 1 workgroups.
+    // One workgroup per piece; rows are split over launches of at most `most`
+    // workgroups, which a single row does not exceed.
     const int64_t ppr = (row_elems + P - 1) / P;
-    const int64_t rows_per_launch = ppr >= 0x7FFFFFFF ? 1 : 0x7FFFFFFF / ppr;
+    const int64_t rows_per_launch = most / ppr;
     const uint32_t last = (uint32_t)(row_elems - (ppr - 1) * P);
     for (int64_t r0 = 0; r0 < n; r0 += rows_per_launch) {
         const int64_t m = n - r0 < rows_per_launch ? n - r0 : rows_per_launch;
@@ -379,24 +379,38 @@ hipError_t acquire_slot(Table& t, PinSlot& ps) {
 
 hipError_t release_slot(Table& t, const PinSlot& ps, hipStream_t s) { return hipEventRecord(t.pin_free[ps.k], s); }
 
-hipError_t launch_segments(const Segment* seg, int n, const WordTail* tail, hipStream_t s) {
-    int k = 0;
-    do {
+hipError_t launch_segments(const Table& t, const Segment* seg, int n, const WordTail* tail, hipStream_t s) {
+    const int64_t most = t.max_items / kSegThreads;  // workgroups of a launch
+    const int64_t words = tail != nullptr ? (tail->n + kSegThreads - 1) / kSegThreads : 0;
+    int64_t done = 0;  // bytes of segment k that earlier launches copy
+    bool finished = false;
+    for (int k = 0; !finished;) {
         SegmentArgs a{};
         for (int j = 0; j < kMaxSegments; j++) a.task0[j] = UINT32_MAX;
         int64_t tasks = 0;
         int used = 0;
-        for (; k < n && used < kMaxSegments; k++) {
-            if (seg[k].bytes <= 0) continue;
-            const int64_t lead = (int64_t)(reinterpret_cast<uintptr_t>(seg[k].dst) & 15);
-            const int64_t more = (lead + seg[k].bytes + kSegPiece - 1) / kSegPiece;
-            if (used > 0 && tasks + more > 0x7FFFFFF0) break;    // the next launch's
-            if (more > 0x7FFFFFF0) return hipErrorInvalidValue;  // above 2 TiB: more than any device holds
-            a.task0[used] = (uint32_t)tasks;
-            a.seg[used++] = seg[k];
-            tasks += more;
+        while (k < n && used < kMaxSegments && tasks < most) {
+            const Segment g{seg[k].src + done, seg[k].dst + done, seg[k].bytes - done};
+            if (g.bytes > 0) {
+                const int64_t lead = (int64_t)(reinterpret_cast<uintptr_t>(g.dst) & 15);
+                const int64_t need = (lead + g.bytes + kSegPiece - 1) / kSegPiece;
+                a.task0[used] = (uint32_t)tasks;
+                a.seg[used] = g;
+                if (need > most - tasks) {  // the rest in the next launch
+                    a.seg[used].bytes = (most - tasks) * kSegPiece - lead;
+                    done += a.seg[used].bytes;
+                    tasks = most;
+                    used++;
+                    break;
+                }
+                tasks += need;
+                used++;
+            }
+            k++;
+            done = 0;
         }
-        if (k == n && tail != nullptr) {  // with the last segments
+        finished = k == n && tasks + words <= most;
+        if (finished && words > 0) {  // with the last segments
             WordArgs w;
             w.task0 = (uint32_t)tasks;
             w.n = tail->n;
@@ -404,8 +418,8 @@ hipError_t launch_segments(const Segment* seg, int n, const WordTail* tail, hipS
             w.at = tail->at;
             w.N = tail->N;
             std::memcpy(w.words, tail->words, sizeof(uint32_t) * (size_t)tail->n);
-            tasks += (tail->n + kSegThreads - 1) / kSegThreads;
-            hipLaunchKernelGGL(copy_segments_words_kernel, dim3((unsigned)tasks), dim3(kSegThreads), 0, s, a, w);
+            hipLaunchKernelGGL(copy_segments_words_kernel, dim3((unsigned)(tasks + words)), dim3(kSegThreads), 0, s, a,
+                               w);
         } else if (used > 0) {
             hipLaunchKernelGGL(copy_segments_kernel, dim3((unsigned)tasks), dim3(kSegThreads), 0, s, a);
         } else {
@@ -413,9 +427,10 @@ hipError_t launch_segments(const Segment* seg, int n, const WordTail* tail, hipS
         }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-    } while (k < n);
+    }
     return hipSuccess;
 }
+static_assert(kMinWorkItems / kSegThreads > kInlineWords / kSegThreads, "a launch holds the word list");
 
 void free_index_manager(Table& t) {
     (void)hipFree(t.order);
@@ -471,7 +486,7 @@ int write_rows(Table& t, int64_t n, const int64_t* idx, const void* const* col_s
                 r0 = r1;
             }
         }
-        const hipError_t e = launch_segments(seg, count, nullptr, s);
+        const hipError_t e = launch_segments(t, seg, count, nullptr, s);
         return e == hipSuccess ? GEAR_OK : hip_fail(e, "row copy launch");
     }
     // The slot list moves to HBM once per chunk for all columns.
@@ -491,13 +506,21 @@ int write_rows(Table& t, int64_t n, const int64_t* idx, const void* const* col_s
             const int64_t rb = (int64_t)t.T * t.elem_bytes[c];
             uint8_t* base = t.col_dev[c];  // the mapped device address for pinned tables
             const uint8_t* sc = static_cast<const uint8_t*>(col_src[c]) + (size_t)off * rb;
+            const int64_t most = t.max_items / kRowThreads;  // workgroups of a launch, 1 KiB each
+            if (rb > most * 1024) {
+                for (int64_t r = 0; r < cnt && e == hipSuccess; r++) {
+                    const Segment g{sc + r * rb, base + idx[off + r] * rb, rb};
+                    e = launch_segments(t, &g, 1, nullptr, s);
+                }
+                continue;
+            }
             const uintptr_t align = reinterpret_cast<uintptr_t>(sc) | reinterpret_cast<uintptr_t>(base) | (uintptr_t)rb;
             if (align % 16 == 0)
-                e = launch_rows<u32x4_t>(t.stage_idx, cnt, sc, base, rb, s);
+                e = launch_rows<u32x4_t>(t.stage_idx, cnt, sc, base, rb, most, s);
             else if (align % 4 == 0)
-                e = launch_rows<uint32_t>(t.stage_idx, cnt, sc, base, rb, s);
+                e = launch_rows<uint32_t>(t.stage_idx, cnt, sc, base, rb, most, s);
             else
-                e = launch_rows<uint8_t>(t.stage_idx, cnt, sc, base, rb, s);
+                e = launch_rows<uint8_t>(t.stage_idx, cnt, sc, base, rb, most, s);
         }
         if (e != hipSuccess) return hip_fail(e, "row scatter");
     }

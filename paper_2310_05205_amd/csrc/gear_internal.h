@@ -45,6 +45,9 @@ constexpr int64_t kStageRows = 1 << 16;
 constexpr int kStageSlots = 4;
 constexpr int64_t kStageSlotBytes = kStageRows * (int64_t)(sizeof(int64_t) + sizeof(uint32_t));
 
+// HIP refuses a launch of 2^32 work items or more; larger work is cut into several.
+constexpr int64_t kMaxWorkItems = 0xFFFFFFFFll;
+
 // Per-slot state of the index manager (host side).
 enum : uint8_t { kSlotFree = 0, kSlotPending = 1, kSlotCommitted = 2, kSlotMark = 3 };
 
@@ -80,6 +83,7 @@ struct Table {
     uint32_t* status = nullptr;       // device status word
     bool cdf_dirty = true;            // the tree does not reflect the priorities
     uint32_t options = 0;             // GEAR_OPT_* bits
+    int64_t max_items = kMaxWorkItems;  // work items of one launch, at most
 
     // TopK scratch (fixed sizes).
     uint32_t* topk_hist = nullptr;    // [kTopkHistRows][kTopkBins] digit histograms, zero between calls
@@ -133,6 +137,12 @@ class AllocHook {
     long count_ = 0;
 };
 
+// Work items of one launch of a new table: GEAR_TEST_MAX_WORK_ITEMS=n (at least
+// kMinWorkItems) in the environment lowers the limit, so that tests see small
+// calls cut into several launches.
+constexpr int64_t kMinWorkItems = 16384;
+int64_t launch_limit();
+
 // Makes the table's device current for the lifetime of the guard.
 class DeviceGuard {
   public:
@@ -182,8 +192,9 @@ struct WordTail {
     int64_t at, N;
 };
 // Copies every segment (device-readable sources and destinations, which do not
-// overlap); empty ones are skipped.  `tail` may be NULL.
-hipError_t launch_segments(const Segment* seg, int n, const WordTail* tail, hipStream_t s);
+// overlap); empty ones are skipped.  `tail` may be NULL.  Segments beyond what one
+// launch takes are cut over several.
+hipError_t launch_segments(const Table& t, const Segment* seg, int n, const WordTail* tail, hipStream_t s);
 // Where a source lives: memory of `device`, page-locked or pageable host memory,
 // or anything else (managed memory, another device).
 enum class Source { kDevice, kPinned, kPageable, kOther };

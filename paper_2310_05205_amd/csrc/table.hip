@@ -49,6 +49,12 @@ AllocHook::AllocHook() {
     if (v != nullptr) fail_at_ = strtol(v, nullptr, 10);
 }
 
+int64_t launch_limit() {
+    const char* v = getenv("GEAR_TEST_MAX_WORK_ITEMS");
+    const int64_t n = v != nullptr ? strtoll(v, nullptr, 10) : kMaxWorkItems;
+    return n < kMinWorkItems ? kMinWorkItems : n < kMaxWorkItems ? n : kMaxWorkItems;
+}
+
 }  // namespace gear
 
 using gear::fail;
@@ -203,6 +209,7 @@ int create_table(const int64_t* elem_bytes, int32_t ncols, int64_t capacity, int
     t->N = capacity;
     t->T = T;
     t->ncols = ncols;
+    t->max_items = gear::launch_limit();
     t->elem_bytes.assign(elem_bytes, elem_bytes + ncols);
     t->col_name = std::move(meta.name);
     t->col_dtype = std::move(meta.dtype);
@@ -397,7 +404,7 @@ extern "C" int gear_insert(gear_table* h, int64_t n, const void* const* col_src,
             seg[count++] = {src, base + (size_t)slot0 * rb, (int64_t)((size_t)first * rb)};
             seg[count++] = {src + (size_t)first * rb, base, (int64_t)((size_t)second * rb)};
         }
-        e = gear::launch_segments(seg, count, in_args ? &tail : nullptr, s);
+        e = gear::launch_segments(*t, seg, count, in_args ? &tail : nullptr, s);
         if (e == hipSuccess && staged) e = gear::release_slot(*t, ps, s);
         if (e != hipSuccess) return hip_fail(e, "gear_insert: launch");
     } else {
