@@ -114,7 +114,8 @@ struct DrawArgs {
 // kernels that hold only the code their columns need: 512 windows of 20 steps
 // of 68, 24, 4 and 4 bytes 4.3 -> 3.6 us).
 struct CollectArgs {
-    int32_t task0[kMaxLaunchCols];  // first task (workgroup) of each column; INT32_MAX past the last
+    int32_t task0[kMaxLaunchCols];  // first task of each column, counted from the launch's first (negative in
+                                    // the later launches of a batch cut over several); INT32_MAX past the last
     const int64_t* idx;     // the caller's draws, unless the pieces compute them
     const int32_t* start;
     uint32_t* status;
@@ -446,7 +447,7 @@ template <int U, bool DRAWS, bool ANY>
 __global__ __launch_bounds__(kThreads) void collect_kernel(CollectArgs a, DrawArgs g) {
     __shared__ Staged st;
     const int32_t task = (int32_t)blockIdx.x;
-    int j = 0, first = 0;
+    int j = 0, first = a.task0[0];
 #pragma unroll
     for (int k0 = 0; k0 < kMaxLaunchCols; k0 += 4) {
 #pragma unroll
@@ -486,6 +487,40 @@ CollectKernel collect_variant(bool draws, bool any) {
     return any ? collect_kernel<U, false, true> : collect_kernel<U, false, false>;
 }
 
+// How column c's batch of B windows of L steps is cut into pieces; returns their
+// number.
+int64_t plan_column(const Table& t, int32_t c, void* out, int32_t B, int32_t L, int unroll, ColTask& ct) {
+    ct.src = t.col_dev[c];
+    ct.out = static_cast<uint8_t*>(out);
+    ct.E = (int32_t)t.elem_bytes[c];  // at most 2^30
+    ct.W = (int64_t)L * ct.E;
+    const uintptr_t oa = reinterpret_cast<uintptr_t>(ct.out);
+    const int64_t elems = (int64_t)kThreads * unroll;  // per piece
+    // A straddling piece stages its windows' offsets, one per thread.
+    const bool straddle = oa % 16 == 0 && ct.W % 16 != 0 && ct.W >= 16 && ct.W * (kThreads - 2) >= elems * 16;
+    if (straddle || (oa % 16 == 0 && ct.W % 16 == 0)) ct.width = 16;
+    else if (oa % 4 == 0 && ct.W % 4 == 0) ct.width = 4;
+    else ct.width = 1;
+    const int64_t piece = elems * ct.width;
+    ct.n = ct.W / ct.width;
+    ct.layout = straddle ? kStraddle : ct.W >= piece ? kWide : kNarrow;
+    if (ct.layout == kStraddle) {
+        ct.recip = ~0ull / (uint64_t)ct.W;
+        ct.magic = ct.W < piece ? (uint32_t)(((1ull << 32) + ct.W - 1) / ct.W) : 0u;
+        return ((int64_t)B * ct.W + piece - 1) / piece;
+    }
+    if (ct.layout == kWide) {
+        ct.recip = ~0ull / (uint64_t)ct.n;
+        return ((int64_t)B * ct.n + elems - 1) / elems;
+    }
+    int64_t wpp = piece / ct.W;
+    if (wpp > kThreads) wpp = kThreads;
+    ct.wpp = (uint16_t)wpp;
+    ct.epw = (uint32_t)(ct.W / ct.width);
+    ct.magic = ct.epw > 1 ? (uint32_t)(((1ull << 32) + ct.epw - 1) / ct.epw) : 0u;
+    return (B + wpp - 1) / wpp;
+}
+
 // The collect launches over ncols requested columns (kMaxLaunchCols per
 // launch).  With `draws`, the windows are those FIFO, LIFO or uniform draws,
 // computed in the kernel, and the first launch's first column writes them to
@@ -498,6 +533,17 @@ int launch_collect(Table* t, const int64_t* d_idx, const int32_t* d_start, const
     for (int j = 0; j < ncols; j++) batch_bytes += (int64_t)B * L * t->elem_bytes[col_ids ? col_ids[j] : j];
     const bool share = !pinned && batch_bytes >= kLongBatch && (t->options & GEAR_OPT_GATHER_SHARE_CU);
     const int unroll = pinned ? kUnrollHost : share ? kUnrollShare : kUnroll;
+
+    // A batch that is refused launches nothing: with several groups of columns,
+    // every group's pieces are counted before the first launch.
+    for (int j0 = 0; j0 < ncols && ncols > kMaxLaunchCols; j0 += kMaxLaunchCols) {
+        int64_t tasks = 0;
+        for (int j = j0; j < ncols && j < j0 + kMaxLaunchCols; j++) {
+            ColTask ct{};
+            tasks += plan_column(*t, col_ids ? col_ids[j] : j, d_out[j], B, L, unroll, ct);
+        }
+        if (tasks > INT32_MAX) return fail(GEAR_E_INVAL, std::string(who) + ": batch too large for one call");
+    }
 
     for (int j0 = 0; j0 < ncols; j0 += kMaxLaunchCols) {
         CollectArgs a{};
@@ -525,51 +571,29 @@ int launch_collect(Table* t, const int64_t* d_idx, const int32_t* d_start, const
         // (measured 1.6% faster on whole 68 KB trajectories).
         const int jend = ncols < j0 + kMaxLaunchCols ? ncols : j0 + kMaxLaunchCols;
         for (int j = jend - 1; j >= j0; j--) {
-            const int c = col_ids ? col_ids[j] : j;
             if (tasks > INT32_MAX) break;  // refused below
             a.task0[launch_cols] = (int32_t)tasks;
             ColTask& ct = a.col[launch_cols++];
-            ct.src = t->col_dev[c];
-            ct.out = static_cast<uint8_t*>(d_out[j]);
-            ct.E = (int32_t)t->elem_bytes[c];  // at most 2^30
-            ct.W = (int64_t)L * ct.E;
+            const int64_t k = plan_column(*t, col_ids ? col_ids[j] : j, d_out[j], B, L, unroll, ct);
             ct.draws_out = draws != nullptr && j == 0;
-            const uintptr_t oa = reinterpret_cast<uintptr_t>(ct.out);
-            const int64_t elems = (int64_t)kThreads * unroll;  // per piece
-            // A straddling piece stages its windows' offsets, one per thread.
-            const bool straddle = oa % 16 == 0 && ct.W % 16 != 0 && ct.W >= 16 && ct.W * (kThreads - 2) >= elems * 16;
-            if (straddle || (oa % 16 == 0 && ct.W % 16 == 0)) ct.width = 16;
-            else if (oa % 4 == 0 && ct.W % 4 == 0) ct.width = 4;
-            else ct.width = 1;
-            const int64_t piece = elems * ct.width;
-            ct.n = ct.W / ct.width;
-            any = any || straddle || ct.width != 16;
-            ct.layout = straddle ? kStraddle : ct.W >= piece ? kWide : kNarrow;
-            if (ct.layout == kStraddle) {
-                ct.recip = ~0ull / (uint64_t)ct.W;
-                ct.magic = ct.W < piece ? (uint32_t)(((1ull << 32) + ct.W - 1) / ct.W) : 0u;
-                tasks += ((int64_t)B * ct.W + piece - 1) / piece;
-            } else if (ct.layout == kWide) {
-                ct.recip = ~0ull / (uint64_t)ct.n;
-                const int64_t k = ((int64_t)B * ct.n + elems - 1) / elems;
-                tasks += k;
-                wide_tasks += k;
-            } else {
-                int64_t wpp = piece / ct.W;
-                if (wpp > kThreads) wpp = kThreads;
-                ct.wpp = (uint16_t)wpp;
-                ct.epw = (uint32_t)(ct.W / ct.width);
-                ct.magic = ct.epw > 1 ? (uint32_t)(((1ull << 32) + ct.epw - 1) / ct.epw) : 0u;
-                tasks += (B + wpp - 1) / wpp;
-            }
+            any = any || ct.layout == kStraddle || ct.width != 16;
+            tasks += k;
+            wide_tasks += ct.layout == kWide ? k : 0;
         }
-        if (tasks > 0x7FFFFFFF) return fail(GEAR_E_INVAL, std::string(who) + ": batch too large for one launch");
+        if (tasks > INT32_MAX) return fail(GEAR_E_INVAL, std::string(who) + ": batch too large for one call");
         const unsigned lds = share ? kShareLds : !pinned && wide_tasks * 2 > tasks ? kWideLds : 0u;
         const CollectKernel kernel = unroll == kUnroll ? collect_variant<kUnroll>(draws != nullptr, any)
                                                        : collect_variant<kUnrollHost>(draws != nullptr, any);
-        hipLaunchKernelGGL(kernel, dim3((unsigned)tasks), dim3(kThreads), lds, s, a, g);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return hip_fail(e, (std::string(who) + ": launch").c_str());
+        // One launch, unless the batch has more pieces than a launch may have
+        // workgroups (128 GiB in elements of 16 bytes).
+        const int64_t most = t->max_items / kThreads;
+        for (int64_t done = 0; done < tasks; done += most) {
+            const int64_t grid = tasks - done < most ? tasks - done : most;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kThreads), lds, s, a, g);
+            hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return hip_fail(e, (std::string(who) + ": launch").c_str());
+            for (int k = 0; k < launch_cols; k++) a.task0[k] -= (int32_t)grid;
+        }
     }
     return GEAR_OK;
 }

@@ -75,6 +75,32 @@ class Runtime:
         return self.gear.gear_table_column(table, c)[0]
 
 
+class ColTask(ctypes.Structure):
+    _fields_ = [("src", ctypes.c_uint64), ("out", ctypes.c_uint64), ("W", ctypes.c_int64), ("n", ctypes.c_int64),
+                ("recip", ctypes.c_uint64), ("E", ctypes.c_int32), ("epw", ctypes.c_uint32),
+                ("magic", ctypes.c_uint32), ("wpp", ctypes.c_uint16), ("width", ctypes.c_uint8),
+                ("layout", ctypes.c_uint8), ("pad", ctypes.c_int64)]
+
+
+class CollectArgs(ctypes.Structure):
+    _fields_ = [("task0", ctypes.c_int32 * 16), ("idx", ctypes.c_uint64), ("start", ctypes.c_uint64),
+                ("status", ctypes.c_uint64), ("N", ctypes.c_int64), ("B", ctypes.c_int32), ("T", ctypes.c_int32),
+                ("L", ctypes.c_int32), ("pad", ctypes.c_int32 * 5), ("col", ColTask * 16)]
+
+
+assert ctypes.sizeof(ColTask) == 64 and CollectArgs.col.offset % 64 == 0
+
+
+def read_collect(name, args):
+    """The arguments of collect_kernel: elements per thread, first tasks, columns."""
+    if "collect_kernel" not in name:
+        return None
+    a = ctypes.cast(args[0], ctypes.POINTER(CollectArgs)).contents
+    used = [k for k in range(16) if a.task0[k] != 0x7FFFFFFF]
+    return (int(name.split("collect_kernelILi")[1][0]), [a.task0[k] for k in used],
+            [{f: getattr(a.col[k], f) for f in ("out", "W", "n", "width", "layout", "wpp", "epw")} for k in used])
+
+
 def read_segments(name, args):
     """The arguments of copy_segments_kernel and copy_segments_words_kernel."""
     if "copy_segments" not in name:

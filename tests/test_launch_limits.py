@@ -93,3 +93,55 @@ def test_insertion(stub, how, elem_bytes, N, T, before, n):
         assert words == (n if n <= 512 else 0)
     if elem_bytes[0] == 68:
         assert launches == 1
+
+
+def gather(rt, elem_bytes, N, T, B, L, shift, fused):
+    """Launches of one gather: their grids, and which bytes of each batch its pieces cover."""
+    t = rt.table(elem_bytes, N, T)
+    prio = np.ones(N, np.uint32)
+    rt.gear.gear_insert(t, N, [rt.device(N * T * e) for e in elem_bytes], prio.ctypes.data)
+    out = [rt.device(B * L * e + 16) + shift for e in elem_bytes]
+    idx, start = rt.device(8 * B), rt.device(4 * B)
+    del rt.launches[:]
+    rt.reader = stub_runtime.read_collect
+    try:
+        if fused:
+            rt.gear.gear_select_collect(t, rt.gear.GEAR_UNIFORM, B, L, 1, idx, start, 0, None, out)
+        else:
+            rt.gear.gear_collect(t, idx, start, B, L, None, out)
+    except rt.gear.GearError as e:
+        return [e.code, len(rt.launches)]
+    covered = {}
+    for name, grid, block, (unroll, task0, cols) in rt.launches:
+        assert block == 256
+        for k, c in enumerate(cols):
+            # The column's pieces that this launch's workgroups take.
+            first = max(0, -task0[k])
+            stop = (task0[k + 1] if k + 1 < len(cols) else grid) - task0[k]
+            stop = min(stop, grid - task0[k])
+            piece = block * unroll * c["width"] if c["layout"] else c["wpp"] * c["W"]
+            a, b = first * piece, min(stop * piece, B * c["W"])
+            if a < b:
+                covered.setdefault(c["out"], []).append((a, a, b - a))
+    whole = all(merged(covered[o]) == [(0, 0, B * L * e)] for o, e in zip(out, elem_bytes))
+    return [whole, len(rt.launches)]
+
+
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("elem_bytes,N,T,B,L,shift", [
+    ([1024, 32, 4], 500000, 200, 1 << 20, 200, 0),   # 222 GB: beyond 128 GiB in 16-byte elements
+    ([4112], 1 << 20, 4, 1 << 24, 1, 0),             # 69 GB of windows just above half a piece
+    ([1028], 1 << 20, 200, 1 << 18, 200, 4),         # 54 GB written in 4-byte elements
+    ([1025, 3], 1 << 16, 200, 1 << 16, 200, 1),      # 13 GB written in bytes
+    ([1 << 30], 2, 150, 1, 150, 0),                  # one window of 150 GiB
+    ([64, 4], 1000, 50, 256, 10, 0),                 # an ordinary call: one launch
+])
+def test_gather(stub, elem_bytes, N, T, B, L, shift, fused):
+    whole, launches = stub_runtime.run(stub, __name__, "gather", elem_bytes, N, T, B, L, shift, fused)
+    assert whole is True
+    assert (launches == 1) == (B == 256)
+
+
+def test_a_refused_gather_launches_nothing(stub):
+    """The second group of 16 columns has 2^31 pieces or more: 20 TB of windows."""
+    assert stub_runtime.run(stub, __name__, "gather", [4] * 16 + [1 << 20], 1 << 20, 4, 1 << 24, 1, 0, False) == [-1, 0]

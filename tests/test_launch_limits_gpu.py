@@ -56,3 +56,33 @@ def test_insertion(limited, cols, how):
             np.testing.assert_array_equal(host(t.column_view(c)), m)
         np.testing.assert_array_equal(t.priorities(), prio)
     assert t.sync() == 0
+
+
+@pytest.mark.parametrize("residency", [gear.GEAR_DEVICE, gear.GEAR_HOST_PINNED])
+@pytest.mark.parametrize("cols,T,B,L", [([1024, 32, 4], 40, 300, 32), ([147, 1, 2, 1], 30, 3001, 13),
+                                        ([20000], 12, 40, 12), ([3, 16, 4] * 7, 25, 500, 9)])
+def test_gather(limited, cols, T, B, L, residency):
+    """Batches of several 64-workgroup launches, wide, narrow and straddling
+    columns, against indexing; with a missing draw and the selection inside."""
+    N = 60
+    rng = np.random.default_rng(B)
+    t = limited(cols, N, T, residency)
+    rows = [rng.integers(0, 256, (N, T, e), dtype=np.uint8) for e in cols]
+    t.insert([r.reshape(N, -1) for r in rows], np.ones(N, np.uint32))
+    say("%s B=%d L=%d residency %d" % (cols[:4], B, L, residency))
+    idx = rng.integers(0, N, B)
+    start = rng.integers(0, T - L + 1, B).astype(np.int32)
+    idx[B // 2] = -1
+    got = t.collect(torch.from_numpy(idx).to(cuda()), torch.from_numpy(start).to(cuda()), L)
+    fidx, fstart, _, fused = t.select_collect(gear.GEAR_UNIFORM, B, L, 7)
+    sidx, sstart, _ = t.select(gear.GEAR_UNIFORM, B, L, 7)
+    assert torch.equal(fidx, sidx) and torch.equal(fstart, sstart)
+    fidx, fstart = host(fidx), host(fstart)
+    steps = np.arange(L)
+    for c, e in enumerate(cols):
+        want = rows[c][idx[:, None], start[:, None] + steps].reshape(B, -1)
+        want[B // 2] = 0
+        np.testing.assert_array_equal(host(got[c]), want)
+        np.testing.assert_array_equal(host(fused[c]),
+                                      rows[c][fidx[:, None], fstart[:, None] + steps].reshape(B, -1))
+    assert t.sync() == 0
