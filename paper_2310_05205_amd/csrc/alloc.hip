@@ -296,15 +296,17 @@ __global__ void copy_list_kernel(const int64_t* __restrict__ src, int64_t n, int
 
 unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 
-// Whether a kernel on the table's device can read `p` (device memory, or
-// pinned / mapped host memory); pageable host memory cannot.
-bool device_readable(const void* p) {
+// Where a kernel on the table's device reads host pointer or device pointer `p`, or
+// NULL for pageable host memory, which it cannot.  Memory that was page-locked
+// after its allocation may have another address on the device.
+const void* device_address(const void* p) {
     hipPointerAttribute_t a;
     if (hipPointerGetAttributes(&a, p) != hipSuccess) {
         (void)hipGetLastError();  // clear the error a pageable pointer leaves
-        return false;
+        return nullptr;
     }
-    return a.type == hipMemoryTypeDevice || a.type == hipMemoryTypeHost || a.type == hipMemoryTypeManaged;
+    if (a.type == hipMemoryTypeHost) return a.devicePointer != nullptr ? a.devicePointer : p;
+    return a.type == hipMemoryTypeDevice || a.type == hipMemoryTypeManaged ? p : nullptr;
 }
 
 // Releases one victim by the removal strategy (host state only).
@@ -330,15 +332,18 @@ int64_t release_victim(Table& t) {
 
 }  // namespace
 
-Source source_kind(const void* p, int device) {
+Source source_kind(const void* p, int device, const void** at) {
     hipPointerAttribute_t a;
+    if (at != nullptr) *at = p;
     if (hipPointerGetAttributes(&a, p) != hipSuccess) {
         (void)hipGetLastError();
         return Source::kPageable;
     }
     if (a.type == hipMemoryTypeUnregistered) return Source::kPageable;
     if (a.type == hipMemoryTypeDevice && a.device == device) return Source::kDevice;
-    return a.type == hipMemoryTypeHost ? Source::kPinned : Source::kOther;
+    if (a.type != hipMemoryTypeHost) return Source::kOther;
+    if (at != nullptr && a.devicePointer != nullptr) *at = a.devicePointer;
+    return Source::kPinned;
 }
 
 bool in_one_allocation(const void* p, int64_t bytes) {
@@ -444,14 +449,14 @@ void free_index_manager(Table& t) {
 }
 
 int write_rows(Table& t, int64_t n, const int64_t* idx, const void* const* col_src, hipStream_t s) {
-    std::vector<bool> kernel_path((size_t)t.ncols);
+    std::vector<const uint8_t*> on_device((size_t)t.ncols);  // NULL for the copies' path
     bool any_kernel = false;
     for (int c = 0; c < t.ncols; c++) {
         const int64_t rb = (int64_t)t.T * t.elem_bytes[c];
         const uint8_t* src = static_cast<const uint8_t*>(col_src[c]);
-        kernel_path[(size_t)c] = device_readable(src);
-        any_kernel = any_kernel || kernel_path[(size_t)c];
-        if (kernel_path[(size_t)c]) continue;
+        on_device[(size_t)c] = static_cast<const uint8_t*>(device_address(src));
+        any_kernel = any_kernel || on_device[(size_t)c] != nullptr;
+        if (on_device[(size_t)c] != nullptr) continue;
         // Pageable host source: one copy per run of consecutive slots.
         uint8_t* hbase = t.residency == GEAR_HOST_PINNED ? t.col_host[c] : t.col_dev[c];
         int64_t r0 = 0;
@@ -471,17 +476,17 @@ int write_rows(Table& t, int64_t n, const int64_t* idx, const void* const* col_s
     // column's rows could be replaced before another column has read them.
     bool one_launch = find_runs(idx, n, true, list, runs);
     for (int c = 0; c < t.ncols && one_launch; c++)
-        one_launch = !kernel_path[(size_t)c] || !meets_table(t, col_src[c], n * t.T * t.elem_bytes[c]);
+        one_launch = on_device[(size_t)c] == nullptr || !meets_table(t, on_device[(size_t)c], n * t.T * t.elem_bytes[c]);
     if (one_launch) {
         Segment seg[GEAR_MAX_COLUMNS * kMaxRuns];
         int count = 0;
         for (int c = 0; c < t.ncols; c++) {
-            if (!kernel_path[(size_t)c]) continue;
+            if (on_device[(size_t)c] == nullptr) continue;
             const int64_t rb = (int64_t)t.T * t.elem_bytes[c];
             int64_t r0 = 0;
             for (int r = 0; r < runs; r++) {
                 const int64_t r1 = r + 1 < runs ? list.end[r] : n;
-                seg[count++] = {static_cast<const uint8_t*>(col_src[c]) + (size_t)r0 * rb,
+                seg[count++] = {on_device[(size_t)c] + (size_t)r0 * rb,
                                 t.col_dev[c] + (size_t)list.first[r] * rb, (r1 - r0) * rb};
                 r0 = r1;
             }
@@ -502,10 +507,10 @@ int write_rows(Table& t, int64_t n, const int64_t* idx, const void* const* col_s
         if (e == hipSuccess) e = release_slot(t, ps, s);
         if (e != hipSuccess) return hip_fail(e, "staging slots");
         for (int c = 0; c < t.ncols && e == hipSuccess; c++) {
-            if (!kernel_path[(size_t)c]) continue;
+            if (on_device[(size_t)c] == nullptr) continue;
             const int64_t rb = (int64_t)t.T * t.elem_bytes[c];
             uint8_t* base = t.col_dev[c];  // the mapped device address for pinned tables
-            const uint8_t* sc = static_cast<const uint8_t*>(col_src[c]) + (size_t)off * rb;
+            const uint8_t* sc = on_device[(size_t)c] + (size_t)off * rb;
             const int64_t most = t.max_items / kRowThreads;  // workgroups of a launch, 1 KiB each
             if (rb > most * 1024) {
                 for (int64_t r = 0; r < cnt && e == hipSuccess; r++) {
@@ -673,13 +678,14 @@ extern "C" int gear_commit(gear_table* h, int64_t n, const int64_t* idx, const u
     hipStream_t s = static_cast<hipStream_t>(stream);
     // Priorities in device or pinned memory are read in place; pageable
     // ones go through the staging slot with the indices.
-    const bool prio_in_place = gear::device_readable(priorities);
+    const uint32_t* const d_prio = static_cast<const uint32_t*>(gear::device_address(priorities));
+    const bool prio_in_place = d_prio != nullptr;
     for (int64_t off = 0; off < n; off += gear::kStageRows) {
         const int64_t cnt = std::min(n - off, gear::kStageRows);
         gear::SlotList list;
         int runs = 0;
         const bool in_args = gear::find_runs(idx + off, cnt, false, list, runs);
-        const uint32_t* p = priorities + off;
+        const uint32_t* p = (prio_in_place ? d_prio : priorities) + off;
         const int64_t pos0 = gear::wrap(t->ord_head + t->n_committed, t->N);
         gear::PinSlot ps;
         hipError_t e = hipSuccess;

@@ -196,9 +196,10 @@ struct WordTail {
 // launch takes are cut over several.
 hipError_t launch_segments(const Table& t, const Segment* seg, int n, const WordTail* tail, hipStream_t s);
 // Where a source lives: memory of `device`, page-locked or pageable host memory,
-// or anything else (managed memory, another device).
+// or anything else (managed memory, another device).  `at`, if given, receives the
+// address at which a kernel reads it.
 enum class Source { kDevice, kPinned, kPageable, kOther };
-Source source_kind(const void* p, int device);
+Source source_kind(const void* p, int device, const void** at = nullptr);
 // Whether bytes [p, p + bytes) lie in one allocation that the runtime knows.
 bool in_one_allocation(const void* p, int64_t bytes);
 // Whether bytes [p, p + bytes) meet a column of the table or its priorities.

@@ -373,14 +373,15 @@ extern "C" int gear_insert(gear_table* h, int64_t n, const void* const* col_src,
         one_launch = gear::source_kind(col_src[c], t->device) == gear::Source::kDevice &&
                      gear::in_one_allocation(col_src[c], bytes) && !gear::meets_table(*t, col_src[c], bytes);
     }
+    const void* prio_at = nullptr;
     gear::Source prio_kind =
-        one_launch ? gear::source_kind(priorities + skip, t->device) : gear::Source::kOther;
+        one_launch ? gear::source_kind(priorities + skip, t->device, &prio_at) : gear::Source::kOther;
     if ((prio_kind == gear::Source::kDevice || prio_kind == gear::Source::kPinned) &&
         (!gear::in_one_allocation(priorities + skip, rows * (int64_t)sizeof(uint32_t)) ||
          gear::meets_table(*t, priorities + skip, rows * (int64_t)sizeof(uint32_t))))
         prio_kind = gear::Source::kOther;
     if (prio_kind != gear::Source::kOther) {
-        const uint32_t* p = priorities + skip;
+        const uint32_t* p = static_cast<const uint32_t*>(prio_at);
         // Short host lists travel in the kernel's arguments: reading them from a
         // new table's staging slot cost its first insertion 15 us.
         const bool in_args = prio_kind == gear::Source::kPageable && rows <= gear::kInlineWords;
