@@ -4,6 +4,8 @@ Row sizes that are and are not multiples of 16 bytes, sources and slots at odd
 addresses, batches that wrap the ring or exceed it, priorities in pageable,
 page-locked and device memory, more columns than one launch takes, and slot lists
 of the index manager as one run, several, descending and scattered."""
+from collections import deque
+
 import numpy as np
 import pytest
 import torch
@@ -61,8 +63,23 @@ def test_ring_insert(cols, T, N, kind):
         t.close()
 
 
+def _runs(slots):
+    """Runs of consecutive slots, ascending or descending, in a list of victims."""
+    runs, k = 0, 0
+    while k < len(slots):
+        step = -1 if k + 1 < len(slots) and slots[k + 1] == slots[k] - 1 else 1
+        k += 1
+        while k < len(slots) and slots[k] == slots[k - 1] + step:
+            k += 1
+        runs += 1
+    return runs
+
+
 @pytest.mark.parametrize("removal", [gear.GEAR_FIFO, gear.GEAR_LIFO])
 def test_managed_insert(removal):
+    """The victims are named by the commit order that the test keeps itself:
+    the oldest under FIFO, the newest under LIFO, in lists of every number of runs
+    that travels in a kernel's arguments and of more."""
     cols, T, N = [5, 64, 33], 3, 40
     rng = np.random.default_rng(int(removal))
     t = gear.Table(cols, N, T)
@@ -70,26 +87,30 @@ def test_managed_insert(removal):
         t.use_allocator(removal)
         model = [np.zeros((N, T * e), np.uint8) for e in cols]
         prio = np.zeros(N, np.uint32)
-        for step in range(40):
+        order, seen = deque(), set()
+        for step in range(60):
             n = int(rng.integers(1, 30))
             idx = t.allocate(n)
-            prio[idx] = 0
-            order = rng.permutation(n) if step % 3 == 0 else np.arange(n)[::-1] if step % 3 == 1 else np.arange(n)
-            idx = np.ascontiguousarray(idx[order])
+            victims = [order.popleft() if removal == gear.GEAR_FIFO else order.pop()
+                       for _ in range(max(0, len(order) + n - N))]
+            seen.add(min(_runs(victims), 9))
+            prio[victims] = 0
+            perm = rng.permutation(n) if step % 3 == 0 else np.arange(n)[::-1] if step % 3 == 1 else np.arange(n)
+            idx = np.ascontiguousarray(idx[perm])
             made = [_rows(n, T * e, step % 16, rng) for e in cols]
             p = rng.integers(1, 1000, n).astype(np.uint32)
+            np.testing.assert_array_equal(t.priorities(), prio)  # the victims and no other slot
             t.write_rows(idx, [d for _, d in made])
             t.commit(idx, _priorities(p, ("pageable", "pinned", "device")[step % 3]))
             for m, (h, _) in zip(model, made):
                 m[idx] = h
             prio[idx] = p
-            committed, pending, free = t.allocator_info()
-            live = np.flatnonzero(t.priorities())
-            assert pending == 0 and committed + free == N and live.size == committed
-            prio[np.setdiff1d(np.arange(N), live)] = 0  # released victims
+            order.extend(idx.tolist())
+            assert t.allocator_info() == (len(order), 0, N - len(order))
             np.testing.assert_array_equal(t.priorities(), prio)
             for c, want in enumerate(model):
                 np.testing.assert_array_equal(host(t.column_view(c)), want)
+        assert {0, 1, 8, 9} <= seen
         assert t.sync() == 0
     finally:
         t.close()

@@ -29,7 +29,11 @@ def test_tree_edges(N, B, options):
     p = rng.integers(1, 1 << 20, N).astype(np.uint32)
     p[rng.random(N) < 0.3] = 0
     p[: N // 2 : 4096] = 0xFFFFFFFF  # sums beyond 32 bits in single tiles
-    p[-1] = 0xFFFFFFFF               # and a draw of the last slot likely
+    global_min = options == gear.GEAR_OPT_IS_GLOBAL_MIN
+    p[p == 1] = 2
+    # A draw of the last slot likely; or the table's only smallest priority there,
+    # in the last chunk.
+    p[-1] = 1 if global_min else 0xFFFFFFFF
     t = gear.Table([], N, 1)
     try:
         t.set_options(options)
@@ -37,13 +41,13 @@ def test_tree_edges(N, B, options):
         for it in range(2):
             say("N=%d B=%d options=%d iteration %d" % (N, B, options, it))
             idx, start, w = t.select(gear.GEAR_PRIORITIZED, B, 1, 77 + it, 0.4, weights=True)
-            st, oidx, ostart, ow = oracle.select(3, p, N, 1, B, 1, 77 + it, 0.4, True)
+            st, oidx, ostart, ow = oracle.select(3, p, N, 1, B, 1, 77 + it, 0.4, True, global_min=global_min)
             assert st == oracle.OK
             np.testing.assert_array_equal(host(idx), oidx)
             np.testing.assert_array_equal(host(start), ostart)
-            if options != gear.GEAR_OPT_IS_GLOBAL_MIN:
-                assert_weights(host(w), ow)
+            assert_weights(host(w), ow)
             new = rng.integers(0, 1 << 20, B).astype(np.uint32)
+            new[new == 1] = 2
             t.update_priorities(idx, torch.from_numpy(new.view(np.int32)).to(cuda()))
             oracle.update(p, oidx, new)
         np.testing.assert_array_equal(t.priorities(), p)
