@@ -395,7 +395,7 @@ def run_insert(args):
     and in steady state (every new trajectory releases a victim), once with
     FIFO and once with LIFO removal.  Per step and removal:
       write_rows  allocate B indices, write B device-resident trajectories into
-                  them with gear_write_rows (one scatter kernel per column),
+                  them with gear_write_rows (one launch for all columns),
                   commit B with device-side priorities;
       insert      the same through one gear_insert call;
     and, FIFO only, the client's own scatter through the column views (torch

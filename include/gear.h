@@ -24,11 +24,14 @@
  *     to the host.  Calls do not wait for the device, except:
  *     gear_table_sync(), which exists to; gear_table_create,
  *     gear_table_use_allocator and gear_table_destroy, which synchronise the
- *     device at set-up and tear-down; calls that pass an index list through
- *     the table's four pinned staging slots (gear_allocate, gear_commit,
- *     gear_write_rows, and gear_insert with an index manager), which wait
- *     only when every slot is still being read by earlier work; and copies
- *     from pageable host memory, which HIP performs synchronously.
+ *     device at set-up and tear-down; calls that pass a host list through
+ *     the table's four pinned staging slots, which wait only when every slot
+ *     is still being read by earlier work (gear_allocate, gear_commit,
+ *     gear_write_rows and gear_insert with an index manager: slot lists of
+ *     more than 8 runs of consecutive slots, rows of the table itself, and
+ *     more than 512 pageable priorities; gear_insert without one: 513 to 65536 pageable priorities
+ *     beside rows in the table's device memory); and copies from pageable
+ *     host memory, which HIP performs synchronously.
  *   - Pointers named d_* are device memory (hipMalloc, or a torch CUDA
  *     tensor's data pointer) on the table's device.  They are owned by the
  *     caller and must stay valid until the enqueued work has completed.
@@ -307,8 +310,9 @@ int gear_commit(gear_table *t, int64_t n, const int64_t *idx, const uint32_t *pr
  *   idx      host int64[n], slots in [0, capacity)
  *   col_src  host array of ncols pointers, col_src[c] holding n*T*elem_bytes[c]
  *            bytes ([n][T][elem_bytes[c]]); device or pinned host memory is
- *            read by one scatter kernel per column, pageable host memory by
- *            one copy per run of consecutive slots
+ *            read by kernels (one launch for all columns when idx is at most 8
+ *            ascending runs of consecutive slots, else one per column), pageable
+ *            host memory by one copy per run
  *
  * Enqueued on `stream`; sources must stay valid until it completes.  The
  * rows of a slot listed twice are written in unspecified order.

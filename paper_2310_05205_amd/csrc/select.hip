@@ -38,7 +38,7 @@ namespace gear {
 namespace {
 
 struct Levels {
-    uint64_t* level[kMaxLevels];   // level 0: tile sums; level l: sums of 256^l tiles
+    uint64_t* level[kMaxLevels];   // level 0: tile sums; level 1: chunk sums; level 2: sums of 256 chunks
     int64_t size[kMaxLevels];
     int nlevels;
     // The top level again (level[nlevels - 1]), so that a search reads it

@@ -315,7 +315,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_hist_kernel(const uint32_t*
                     atomicAdd(&copy[p != 0u ? d : pad], 1u);
                 }
             }
-            } else {
+        } else {
             // The keys of the chosen prefix are the priorities of one range:
             // one compare each, and the key only for those inside.
 #pragma unroll
@@ -666,7 +666,7 @@ __global__ __launch_bounds__(kEmitThreads) void topk_rank_emit_kernel(const uint
                                                                       int64_t* __restrict__ idx,
                                                                       int32_t* __restrict__ start,
                                                                       float* __restrict__ w, uint32_t* status,
-                                                                      int rows0, uint32_t* __restrict__ hist) {
+                                                                      int used_rows, uint32_t* __restrict__ hist) {
     __shared__ uint4 staged[kTopkMaxK / 4];
     const int tid = (int)threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -705,7 +705,7 @@ __global__ __launch_bounds__(kEmitThreads) void topk_rank_emit_kernel(const uint
             if (e < fill) staged[e] = keep_below(v[k - 1], e, lim);
         }
     }
-    for (int h = (int)blockIdx.x * kEmitThreads + tid; h < (2 + rows0) * kBins; h += (int)gridDim.x * kEmitThreads)
+    for (int h = (int)blockIdx.x * kEmitThreads + tid; h < used_rows * kBins; h += (int)gridDim.x * kEmitThreads)
         hist[h] = 0u;  // every digit pass of this call is done
     if (blockIdx.x == 0 && tid == 0 && (st.flags & kInconsistent)) atomicOr(status, GEAR_STATUS_INTERNAL);
     __syncthreads();
@@ -780,9 +780,9 @@ hipError_t launch_topk(Table& t, int32_t K, int32_t L, uint64_t seed, int64_t* i
                            states + kPasses, sel_p, sel_slot);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        // The digit histograms were not used: -2 rows, none to clear.
+        // The digit histograms were not used: no rows to clear.
         hipLaunchKernelGGL(topk_rank_emit_kernel, rank_grid, dim3(kEmitThreads), 0, s, sel_p, sel_slot,
-                           states + kPasses, K, (uint64_t)(t.T - L + 1), seed, idx, start, w, t.status, -2,
+                           states + kPasses, K, (uint64_t)(t.T - L + 1), seed, idx, start, w, t.status, 0,
                            t.topk_hist);
         return hipGetLastError();
     }
@@ -806,8 +806,7 @@ hipError_t launch_topk(Table& t, int32_t K, int32_t L, uint64_t seed, int64_t* i
                        (uint32_t)K, t.topk_hist, t.topk_local, grid, states, sel_p, sel_slot);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(topk_rank_emit_kernel, rank_grid, dim3(kEmitThreads), 0, s, sel_p, sel_slot, state, K,
-                       (uint64_t)(t.T - L + 1), seed, idx, start, w, t.status,
-                       rows0, t.topk_hist);
+                       (uint64_t)(t.T - L + 1), seed, idx, start, w, t.status, 2 + rows0, t.topk_hist);
     return hipGetLastError();
 }
 
